@@ -5,7 +5,7 @@
  * Section 5.1 of the DualSPHysics v5.0 paper (arXiv 2104.00537), into a
  * neighbour list (NL), a particle interaction (PI) and a system update (SU):
  *
- *   sph_bin_cells        NL: cell keys, stable radix sort, cell ranges, and the
+ *   sph_bin_cells        NL: cell keys, stable sort by key, cell ranges, and the
  *                        particle arrays reordered into sorted SoA (plus the
  *                        per-particle data the interaction reads).
  *   sph_interact         PI: continuity and momentum sums over the neighbours
@@ -549,7 +549,7 @@ sph_status sph_floating_step(const sph_params* p, int64_t n, int32_t phase, cons
  * offsets[s+1]) of the packed arrays and the cell keys [cbase_s, cbase_s +
  * C_s] (C_s = its total cells; the last key is for its particles outside its
  * grid), with cbase_s the sum of C + 1 over the slots before it.  So one
- * radix sort, one set of cell ranges, one interaction launch and one update
+ * sort, one set of cell ranges, one interaction launch and one update
  * serve every case, and every slot keeps its particle range through every
  * sort; results of a case do not depend on the other cases in the batch.
  * Packed arrays always have three components: a 2-D case (x, z) is stored as

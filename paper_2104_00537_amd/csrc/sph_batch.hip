@@ -1,7 +1,7 @@
 // Batched cases (continuous batching): n_slots independent cases packed into
 // one set of arrays.  Slot s owns particles [off_s, off_s + n_s) and cell keys
 // [cbase_s, cbase_s + ncell_s] (the last one for its particles outside its
-// grid), so one radix sort, one set of cell ranges, one interaction launch
+// grid), so one sort, one set of cell ranges, one interaction launch
 // and one update serve every case with its own constants, dt and t, and
 // every slot keeps its particle range through every sort.
 #include "sph_dev.h"
@@ -11,28 +11,78 @@
 
 namespace sph {
 
-__global__ void k_batch_cell_keys(const SlotEntry* __restrict__ tab, int ns, int64_t n,
-                                  const double* __restrict__ pos, const uint8_t* __restrict__ type,
-                                  uint32_t* __restrict__ key, SlotAccum* __restrict__ acc,
-                                  uint32_t* __restrict__ disp) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Keys and counts of every slot's cells, as the single-case k_count_cells;
+// each slot's last key holds its excluded particles, which are counted like
+// a cell (one atomic per wavefront and slot) but ranked in input order.
+__global__ __launch_bounds__(kBlock) void k_batch_count_cells(
+    const SlotEntry* __restrict__ tab, int ns, int64_t n, const double* __restrict__ pos,
+    const uint8_t* __restrict__ type, uint32_t* __restrict__ key, uint32_t* __restrict__ rank,
+    uint32_t* __restrict__ count, uint32_t* __restrict__ xcount, uint32_t* __restrict__ xslot,
+    SlotAccum* __restrict__ acc, uint32_t* __restrict__ disp) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < (int64_t)ns * kAccCopies) acc[i] = SlotAccum{0u, 0u, 0u, 0u, 0ull, 0ull};
   if (i < (int64_t)ns * kDispSlots) disp[i] = 0u;  // nothing moved since this binning
+  const int s = i < n ? find_slot(tab, ns, i) : -1;
+  uint32_t k = 0;
+  bool excluded = false;
+  if (i < n) {
+    const uint32_t lk = cell_key_local(tab[s].kp, pos, type, n, i);
+    excluded = lk == tab[s].kp.ncell_total;
+    k = tab[s].cbase + lk;
+  }
+  const int lane = threadIdx.x & 63;
+  const uint64_t mask = __ballot(excluded);
+  if (lane == 0 && i < n) xcount[i >> 6] = (uint32_t)__popcll(mask);
+  uint32_t r = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+  if (i < n && i == tab[s].off) xslot[s] = r;
+  bool pend = excluded;
+  while (__ballot(pend) != 0ull) {
+    const int leader = (int)__builtin_ctzll(__ballot(pend));
+    const uint32_t kl = (uint32_t)__builtin_amdgcn_readlane((int)k, leader);
+    const uint64_t same = __ballot(pend && k == kl);
+    if (lane == leader) atomicAdd(&count[kl], (uint32_t)__popcll(same));
+    pend = pend && k != kl;
+  }
+  const uint32_t rc = count_in_cell(i < n && !excluded, k, count);
   if (i >= n) return;
-  const int s = find_slot(tab, ns, i);
-  key[i] = tab[s].cbase + cell_key_local(tab[s].kp, pos, type, n, i);
+  if (!excluded) r = rc;
+  key[i] = k;
+  rank[i] = r;
 }
 
-__global__ void k_batch_reorder(const SlotEntry* __restrict__ tab, int ns, int64_t n,
-                                const uint32_t* __restrict__ perm, const uint32_t* __restrict__ key,
-                                sph_state in, sph_state out, sph_state cin, sph_state cout,
-                                int carry, float4* __restrict__ pr, float4* __restrict__ vp,
-                                uint32_t* __restrict__ err, uint32_t* __restrict__ slot_err) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The members of each cell in its range (in any order), a slot's excluded
+// particles in theirs (in input order: the excluded particles before this one
+// in the whole batch less those before the slot).
+__global__ __launch_bounds__(kBlock) void k_batch_place(
+    const SlotEntry* __restrict__ tab, int ns, int64_t n, const uint32_t* __restrict__ key,
+    const uint32_t* __restrict__ rank, const uint32_t* __restrict__ cell_start,
+    const uint32_t* __restrict__ xstart, const uint32_t* __restrict__ xslot,
+    uint32_t* __restrict__ member) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
+  const uint32_t k = key[i];
+  uint32_t r = rank[i];
   const int s = find_slot(tab, ns, i);
-  if (reorder_one(tab[s].kp, n, i, perm[i], key[i] - tab[s].cbase, in, out, cin, cout, carry, pr,
-                  vp)) {
+  if (k - tab[s].cbase == tab[s].kp.ncell_total)
+    r += xstart[i >> 6] - (xstart[tab[s].off >> 6] + xslot[s]);
+  member[cell_start[k] + r] = (uint32_t)i;
+}
+
+__global__ __launch_bounds__(kBlock) void k_batch_reorder(
+    const SlotEntry* __restrict__ tab, int ns, int64_t n, const uint32_t* __restrict__ member,
+    const uint32_t* __restrict__ ikey, const uint32_t* __restrict__ cell_start,
+    uint32_t* __restrict__ perm, uint32_t* __restrict__ key, sph_state in, sph_state out,
+    sph_state cin, sph_state cout, int carry, float4* __restrict__ pr, float4* __restrict__ vp,
+    uint32_t* __restrict__ err, uint32_t* __restrict__ slot_err) {
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (t >= n) return;
+  const uint32_t src = member[t], k = ikey[src];
+  const int s = find_slot(tab, ns, t);  // (every slot keeps its particle range)
+  const uint32_t lk = k - tab[s].cbase;
+  const int64_t i = lk < tab[s].kp.ncell_total ? stable_slot(member, cell_start, k, src) : t;
+  perm[i] = src;
+  key[i] = k;
+  if (reorder_one(tab[s].kp, n, i, src, lk, in, out, cin, cout, carry, pr, vp)) {
     set_error(err, SPH_ERR_EXCLUDED);
     set_error(&slot_err[s], SPH_ERR_EXCLUDED);
   }
@@ -394,16 +444,20 @@ hipError_t launch_batch_bin_cells(const BatchDesc& B, const sph_state& in, sph_s
   SlotAccum* sacc = ws_ptr<SlotAccum>(ws, W.accum);
   const int64_t nd = (int64_t)B.n_slots * (kDispSlots > kAccCopies ? kDispSlots : kAccCopies);
   const int64_t nk = n > nd ? n : nd;
-  hipLaunchKernelGGL(k_batch_cell_keys, dim3(grid_for(nk)), dim3(kBlock), 0, st, tab, B.n_slots,
-                     n, in.pos, in.type, ws_ptr<uint32_t>(ws, W.base.keyA), sacc,
+  uint32_t* ikey = ws_ptr<uint32_t>(ws, W.base.keyA);
+  uint32_t* rank = ws_ptr<uint32_t>(ws, W.base.rank);
+  uint32_t* member = ws_ptr<uint32_t>(ws, W.base.keyB);
+  uint32_t* xcount = ws_ptr<uint32_t>(ws, W.base.xcount);
+  uint32_t* xslot = ws_ptr<uint32_t>(ws, W.xslot);
+  launch_zero_cells(cell_start, B.key_cells, st);
+  hipLaunchKernelGGL(k_batch_count_cells, dim3(grid_for(nk)), dim3(kBlock), 0, st, tab, B.n_slots,
+                     n, in.pos, in.type, ikey, rank, cell_start, xcount, xslot, sacc,
                      ws_ptr<uint32_t>(ws, W.disp));
-  const uint32_t last_key = (uint32_t)(B.key_cells - 1);
+  launch_scan_cells(cell_start, B.key_cells, xcount, n, ws_ptr<uint32_t>(ws, W.base.scan_part),
+                    st);
   if (n > 0) {
-    const hipError_t e = radix_sort(n, last_key, key, perm, ws, st);
-    if (e != hipSuccess) return e;
-  }
-  launch_cell_start(key, n, last_key + 1, cell_start, st);
-  if (n > 0) {
+    hipLaunchKernelGGL(k_batch_place, dim3(grid_for(n)), dim3(kBlock), 0, st, tab, B.n_slots, n,
+                       ikey, rank, cell_start, xcount, xslot, member);
     sph_state ci{}, co{};
     const int carry = (cin && cout) ? 1 : 0;
     if (carry) {
@@ -411,9 +465,9 @@ hipError_t launch_batch_bin_cells(const BatchDesc& B, const sph_state& in, sph_s
       co = *cout;
     }
     hipLaunchKernelGGL(k_batch_reorder, dim3(grid_for(n)), dim3(kBlock), 0, st, tab, B.n_slots, n,
-                       perm, key, in, out, ci, co, carry, ws_ptr<float4>(ws, W.base.view_pr),
-                       ws_ptr<float4>(ws, W.base.view_vp), ws_ptr<uint32_t>(ws, W.base.err),
-                       ws_ptr<uint32_t>(ws, W.slot_err));
+                       member, ikey, cell_start, perm, key, in, out, ci, co, carry,
+                       ws_ptr<float4>(ws, W.base.view_pr), ws_ptr<float4>(ws, W.base.view_vp),
+                       ws_ptr<uint32_t>(ws, W.base.err), ws_ptr<uint32_t>(ws, W.slot_err));
   }
   return hipGetLastError();
 }

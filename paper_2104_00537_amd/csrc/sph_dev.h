@@ -48,6 +48,44 @@ __device__ inline uint32_t cell_key_local(const KParams& kp, const double* __res
   return (uint32_t)(c[0] + nc[0] * (c[1] + nc[1] * c[2]));
 }
 
+// Counts the calling lane's particle in its cell k (lanes that take part, in
+// any combination) and returns a rank of its own there.  Neighbouring lanes
+// of one cell make one atomic: an input that a step before left sorted has
+// its cells' members in runs.
+__device__ inline uint32_t count_in_cell(bool take, uint32_t k, uint32_t* __restrict__ count) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t prev = (uint32_t)__shfl_up((int)k, 1, 64);
+  const uint64_t taking = __ballot(take);
+  const bool before = lane > 0 && ((taking >> (lane - 1)) & 1ull);
+  const bool head = take && !(before && prev == k);
+  const uint64_t heads = __ballot(head);
+  // the run's first lane, and one past its last: the next head or idle lane
+  const uint64_t upto = (2ull << lane) - 1ull;  // (lanes 0..lane)
+  const int first = 63 - (int)__builtin_clzll((heads & upto) | 1ull);
+  const uint64_t stop = (heads | ~taking) & ~((2ull << first) - 1ull);
+  const int end = stop ? (int)__builtin_ctzll(stop) : 64;
+  uint32_t base = 0;
+  if (head) base = atomicAdd(&count[k], (uint32_t)(end - lane));
+  base = (uint32_t)__shfl((int)base, first, 64);
+  return base + (uint32_t)(lane - first);
+}
+
+// The sorted index of particle src among the members of its cell k: the
+// cell's first index plus the members with a lower input index (ties of the
+// stable sort keep input order).
+__device__ inline int64_t stable_slot(const uint32_t* __restrict__ member,
+                                      const uint32_t* __restrict__ cell_start, uint32_t k,
+                                      uint32_t src) {
+  const uint32_t c0 = cell_start[k], c1 = cell_start[k + 1];
+  uint32_t below = 0, m = c0;
+  for (; m + 4u <= c1; m += 4u) {  // (coarse cells: loads in flight together)
+    const uint32_t a = member[m], b = member[m + 1u], c = member[m + 2u], d = member[m + 3u];
+    below += (a < src ? 1u : 0u) + (b < src ? 1u : 0u) + (c < src ? 1u : 0u) + (d < src ? 1u : 0u);
+  }
+  for (; m < c1; ++m) below += member[m] < src ? 1u : 0u;
+  return (int64_t)c0 + below;
+}
+
 // (rho/rho0)^gamma - 1 of the Tait equation (Eq. 28: P = B_t times this), in
 // FP64; for gamma = 7 as the expansion of (1+u)^7 - 1 in u = rho/rho0 - 1,
 // which keeps the small pressures of a nearly incompressible fluid free of
@@ -79,26 +117,31 @@ __device__ inline bool reorder_one(const KParams& kp, int64_t n, int64_t i, int6
                                    uint32_t lkey, const sph_state& in, const sph_state& out,
                                    const sph_state& cin, const sph_state& cout, int carry,
                                    float4* __restrict__ pr, float4* __restrict__ vp) {
+  // (all loads first: the compiler cannot move them across the stores)
   double x[3] = {0.0, 0.0, 0.0};
   float v[3] = {0.f, 0.f, 0.f};
-  const bool live = !(in.type[src] & SPH_EXCLUDED);
   for (int d = 0; d < kp.dim; ++d) {
     x[d] = in.pos[d * n + src];
-    if (live) x[d] = wrap_coord(kp, d, x[d]);
     v[d] = in.vel[d * n + src];
+  }
+  const float rho = in.rho[src];
+  uint8_t t = in.type[src];
+  const bool ids = in.id && out.id;
+  const uint32_t id = ids ? in.id[src] : 0u;
+  const bool live = !(t & SPH_EXCLUDED);
+  for (int d = 0; d < kp.dim; ++d) {
+    if (live) x[d] = wrap_coord(kp, d, x[d]);
     out.pos[d * n + i] = x[d];
     out.vel[d * n + i] = v[d];
   }
-  const float rho = in.rho[src];
   out.rho[i] = rho;
-  uint8_t t = in.type[src];
   bool newly = false;
   if (lkey == kp.ncell_total && !(t & SPH_EXCLUDED)) {
     t |= SPH_EXCLUDED;
     newly = true;
   }
   out.type[i] = t;
-  if (in.id && out.id) out.id[i] = in.id[src];
+  if (ids) out.id[i] = id;
   if (in.normal && out.normal)
     for (int d = 0; d < kp.dim; ++d) out.normal[d * n + i] = in.normal[d * n + src];
   if (in.vel64 && out.vel64) {  // an all-FP64 state's velocities and densities

@@ -10,9 +10,9 @@
 namespace sph {
 
 constexpr int kBlock = 256;        // threads per workgroup (4 wave64)
-constexpr int kSortItems = 8;      // keys per thread per radix tile
-constexpr int kSortTile = kBlock * kSortItems;
-constexpr int kScanTile = kBlock * 8;
+constexpr int kScanItems = 8;      // entries per thread of a scan tile
+constexpr int kScanTile = kBlock * kScanItems;
+constexpr int kScanBlocks = 2048;  // most blocks (chunks) of the scan of the cells
 constexpr int kViewPad = 8;        // spare float4 entries after each interaction view
 constexpr int kFrameCells = 8;     // x offsets in the views are taken per block of 8 cells
 constexpr uint32_t kXcds = 8;      // accelerator complex dies of the MI355X
@@ -159,9 +159,10 @@ constexpr int64_t kLanesMaxN = 131072;
 // Workspace layout (offsets in bytes, each region 256-aligned).
 struct WsLayout {
   size_t err;        // the WsHeader (offset 0)
-  size_t keyA, valA, keyB, valB;   // radix sort ping-pong buffers, n each
-  size_t hist;       // uint32 [bins * nblk_sort] digit counts / offsets
-  size_t scan_part;  // uint32 partial sums of the offset scan
+  size_t keyA, rank, keyB;   // uint32 [n] each: keys by input index, rank of a
+                             // particle in its cell as counted, cells' members
+  size_t xcount;     // uint32 [n / 64]: excluded particles per wavefront, then their offsets
+  size_t scan_part;  // uint32 [kScanBlocks]: sums of the scan's chunks
   size_t view_pr;    // float4 [n]: cell-relative position, signed density
   size_t view_vp;    // float4 [n]: velocity, pressure
   size_t red;        // BlockRed [nblk_interact]
@@ -169,7 +170,7 @@ struct WsLayout {
   size_t fpart;      // double [SPH_MAX_BODIES][kFloatParts][kFloatSums]: body partial sums
   size_t fmotion;    // double [SPH_MAX_BODIES][kFloatMotion]: rigid motion of each body
   size_t total;
-  int64_t nblk_sort, nblk_interact, hist_len, scan_parts;
+  int64_t nblk_interact;
 };
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
@@ -177,21 +178,16 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 inline WsLayout ws_layout(int64_t n) {
   WsLayout L{};
   const size_t nn = (size_t)(n > 0 ? n : 1);
-  L.nblk_sort = (n + kSortTile - 1) / kSortTile;
-  if (L.nblk_sort < 1) L.nblk_sort = 1;
   // one per-block partial result per interaction block of kBlock targets
   L.nblk_interact = (n + kBlock - 1) / kBlock;
   if (L.nblk_interact < 1) L.nblk_interact = 1;
-  L.hist_len = 256 * L.nblk_sort;
-  L.scan_parts = (L.hist_len + kScanTile - 1) / kScanTile;
   size_t off = 0;
   L.err = off; off = align_up(off + sizeof(WsHeader));
   L.keyA = off; off = align_up(off + 4 * nn);
-  L.valA = off; off = align_up(off + 4 * nn);
+  L.rank = off; off = align_up(off + 4 * nn);
   L.keyB = off; off = align_up(off + 4 * nn);
-  L.valB = off; off = align_up(off + 4 * nn);
-  L.hist = off; off = align_up(off + 4 * (size_t)L.hist_len);
-  L.scan_part = off; off = align_up(off + 4 * (size_t)L.scan_parts + 4);
+  L.xcount = off; off = align_up(off + 4 * ((nn + 63) / 64));
+  L.scan_part = off; off = align_up(off + 4 * (size_t)kScanBlocks);
   // the views carry kViewPad spare entries: the interaction reads candidates
   // in groups of 4 with scalar loads that may run past the last particle
   L.view_pr = off; off = align_up(off + 16 * (nn + kViewPad));
@@ -208,10 +204,11 @@ inline WsLayout ws_layout(int64_t n) {
 
 // A batch workspace: the single-case layout for all packed particles, then
 // per-slot accumulators, motion table, error words and displacement records
-// (kDispSlots words per slot, as the single-case record).
+// (kDispSlots words per slot, as the single-case record) and the ranks of the
+// slots' first particles among their wavefronts' excluded ones.
 struct BatchWsLayout {
   WsLayout base;
-  size_t accum, motion, slot_err, disp, total;
+  size_t accum, motion, slot_err, disp, xslot, total;
 };
 
 inline BatchWsLayout batch_ws_layout(int32_t n_slots, int64_t n) {
@@ -223,6 +220,7 @@ inline BatchWsLayout batch_ws_layout(int32_t n_slots, int64_t n) {
   B.motion = off; off = align_up(off + sizeof(SlotMotion) * ns);
   B.slot_err = off; off = align_up(off + sizeof(uint32_t) * ns);
   B.disp = off; off = align_up(off + sizeof(uint32_t) * kDispSlots * ns);
+  B.xslot = off; off = align_up(off + sizeof(uint32_t) * ns);
   B.total = off;
   return B;
 }

@@ -18,12 +18,12 @@ struct BatchDesc {
   uint32_t flags;     // SPH_BATCH_* flags of sph_batch_describe
   uint32_t lanes;     // interaction lanes over all slots
 };
-int key_bits(uint32_t ncell_total);
-void exclusive_scan(uint32_t* data, int64_t len, uint32_t* part, hipStream_t st);
-hipError_t radix_sort(int64_t n, uint32_t max_key, uint32_t* key_out, uint32_t* perm_out,
-                      void* ws, hipStream_t st);
-void launch_cell_start(const uint32_t* key, int64_t n, uint32_t last_key, uint32_t* cell_start,
-                       hipStream_t st);
+// The counting sort's shared steps (see sph_bin.hip): clears the counts of
+// the cells; turns them, and the numbers of excluded particles per wavefront,
+// into first sorted indices (cell_start gets cells + 1 entries).
+void launch_zero_cells(uint32_t* cell_start, int64_t cells, hipStream_t st);
+void launch_scan_cells(uint32_t* cell_start, int64_t cells, uint32_t* xcount, int64_t n,
+                       uint32_t* sums, hipStream_t st);
 
 hipError_t launch_bin_cells(const KParams& kp, int64_t n, const sph_state& in, sph_state& out,
                             const sph_state* cin, sph_state* cout, uint32_t* key,
