@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_place(
     const SlotEntry* __restrict__ tab, int ns, int64_t n, const uint32_t* __restrict__ key,
     const uint32_t* __restrict__ rank, const uint32_t* __restrict__ cell_start,
     const uint32_t* __restrict__ xstart, const uint32_t* __restrict__ xslot,
-    uint32_t* __restrict__ member) {
+    uint2* __restrict__ member) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
   const uint32_t k = key[i];
@@ -65,18 +65,18 @@ __global__ __launch_bounds__(kBlock) void k_batch_place(
   const int s = find_slot(tab, ns, i);
   if (k - tab[s].cbase == tab[s].kp.ncell_total)
     r += xstart[i >> 6] - (xstart[tab[s].off >> 6] + xslot[s]);
-  member[cell_start[k] + r] = (uint32_t)i;
+  member[cell_start[k] + r] = make_uint2((uint32_t)i, k);
 }
 
 __global__ __launch_bounds__(kBlock) void k_batch_reorder(
-    const SlotEntry* __restrict__ tab, int ns, int64_t n, const uint32_t* __restrict__ member,
-    const uint32_t* __restrict__ ikey, const uint32_t* __restrict__ cell_start,
+    const SlotEntry* __restrict__ tab, int ns, int64_t n, const uint2* __restrict__ member,
+    const uint32_t* __restrict__ cell_start,
     uint32_t* __restrict__ perm, uint32_t* __restrict__ key, sph_state in, sph_state out,
     sph_state cin, sph_state cout, int carry, float4* __restrict__ pr, float4* __restrict__ vp,
     uint32_t* __restrict__ err, uint32_t* __restrict__ slot_err) {
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (t >= n) return;
-  const uint32_t src = member[t], k = ikey[src];
+  const uint32_t src = member[t].x, k = member[t].y;
   const int s = find_slot(tab, ns, t);  // (every slot keeps its particle range)
   const uint32_t lk = k - tab[s].cbase;
   const int64_t i = lk < tab[s].kp.ncell_total ? stable_slot(member, cell_start, k, src) : t;
@@ -446,7 +446,7 @@ hipError_t launch_batch_bin_cells(const BatchDesc& B, const sph_state& in, sph_s
   const int64_t nk = n > nd ? n : nd;
   uint32_t* ikey = ws_ptr<uint32_t>(ws, W.base.keyA);
   uint32_t* rank = ws_ptr<uint32_t>(ws, W.base.rank);
-  uint32_t* member = ws_ptr<uint32_t>(ws, W.base.keyB);
+  uint2* member = ws_ptr<uint2>(ws, W.base.member);
   uint32_t* xcount = ws_ptr<uint32_t>(ws, W.base.xcount);
   uint32_t* xslot = ws_ptr<uint32_t>(ws, W.xslot);
   launch_zero_cells(cell_start, B.key_cells, st);
@@ -465,7 +465,7 @@ hipError_t launch_batch_bin_cells(const BatchDesc& B, const sph_state& in, sph_s
       co = *cout;
     }
     hipLaunchKernelGGL(k_batch_reorder, dim3(grid_for(n)), dim3(kBlock), 0, st, tab, B.n_slots, n,
-                       member, ikey, cell_start, perm, key, in, out, ci, co, carry,
+                       member, cell_start, perm, key, in, out, ci, co, carry,
                        ws_ptr<float4>(ws, W.base.view_pr), ws_ptr<float4>(ws, W.base.view_vp),
                        ws_ptr<uint32_t>(ws, W.base.err), ws_ptr<uint32_t>(ws, W.slot_err));
   }

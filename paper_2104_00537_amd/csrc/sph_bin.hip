@@ -191,29 +191,30 @@ void launch_scan_cells(uint32_t* cell_start, int64_t cells, uint32_t* xcount, in
 }
 
 // ------------------------------------------------------------- placement --
-// The members of each cell in its range (in any order), excluded particles in
-// theirs (in input order).
+// The members of each cell, {input index, key}, in its range (in any order),
+// excluded particles in theirs (in input order).
 __global__ __launch_bounds__(kBlock) void k_place(int64_t n, uint32_t ncell_total,
                                                   const uint32_t* __restrict__ key,
                                                   const uint32_t* __restrict__ rank,
                                                   const uint32_t* __restrict__ cell_start,
                                                   const uint32_t* __restrict__ xstart,
-                                                  uint32_t* __restrict__ member) {
+                                                  uint2* __restrict__ member) {
   const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   if (i >= n) return;
   const uint32_t k = key[i];
-  member[(k < ncell_total ? cell_start[k] : xstart[i >> 6]) + rank[i]] = (uint32_t)i;
+  member[(k < ncell_total ? cell_start[k] : xstart[i >> 6]) + rank[i]] =
+      make_uint2((uint32_t)i, k);
 }
 
 // --------------------------------------------------------------- reorder --
 __global__ __launch_bounds__(kBlock) void k_reorder(
-    KParams kp, int64_t n, const uint32_t* __restrict__ member, const uint32_t* __restrict__ ikey,
+    KParams kp, int64_t n, const uint2* __restrict__ member,
     const uint32_t* __restrict__ cell_start, uint32_t* __restrict__ perm,
     uint32_t* __restrict__ key, sph_state in, sph_state out, sph_state cin, sph_state cout,
     int carry, float4* __restrict__ pr, float4* __restrict__ vp, uint32_t* __restrict__ err) {
   const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   if (t >= n) return;
-  const uint32_t src = member[t], k = ikey[src];
+  const uint32_t src = member[t].x, k = member[t].y;
   const int64_t i = k < kp.ncell_total ? stable_slot(member, cell_start, k, src) : t;
   perm[i] = src;
   key[i] = k;
@@ -269,7 +270,7 @@ hipError_t launch_bin_cells(const KParams& kp, int64_t n, const sph_state& in, s
   const WsLayout L = ws_layout(n);
   uint32_t* ikey = ws_ptr<uint32_t>(ws, L.keyA);
   uint32_t* rank = ws_ptr<uint32_t>(ws, L.rank);
-  uint32_t* member = ws_ptr<uint32_t>(ws, L.keyB);
+  uint2* member = ws_ptr<uint2>(ws, L.member);
   uint32_t* xcount = ws_ptr<uint32_t>(ws, L.xcount);
   const unsigned gridn = (unsigned)((n + kBlock - 1) / kBlock);
   launch_zero_cells(cell_start, kp.ncell_total, st);
@@ -287,7 +288,7 @@ hipError_t launch_bin_cells(const KParams& kp, int64_t n, const sph_state& in, s
       ci = *cin;
       co = *cout;
     }
-    hipLaunchKernelGGL(k_reorder, dim3(gridn), dim3(kBlock), 0, st, kp, n, member, ikey,
+    hipLaunchKernelGGL(k_reorder, dim3(gridn), dim3(kBlock), 0, st, kp, n, member,
                        cell_start, perm, key, in, out, ci, co, carry,
                        ws_ptr<float4>(ws, L.view_pr), ws_ptr<float4>(ws, L.view_vp),
                        ws_ptr<uint32_t>(ws, L.err));

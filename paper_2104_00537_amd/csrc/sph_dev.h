@@ -73,16 +73,17 @@ __device__ inline uint32_t count_in_cell(bool take, uint32_t k, uint32_t* __rest
 // The sorted index of particle src among the members of its cell k: the
 // cell's first index plus the members with a lower input index (ties of the
 // stable sort keep input order).
-__device__ inline int64_t stable_slot(const uint32_t* __restrict__ member,
+__device__ inline int64_t stable_slot(const uint2* __restrict__ member,
                                       const uint32_t* __restrict__ cell_start, uint32_t k,
                                       uint32_t src) {
   const uint32_t c0 = cell_start[k], c1 = cell_start[k + 1];
   uint32_t below = 0, m = c0;
   for (; m + 4u <= c1; m += 4u) {  // (coarse cells: loads in flight together)
-    const uint32_t a = member[m], b = member[m + 1u], c = member[m + 2u], d = member[m + 3u];
+    const uint32_t a = member[m].x, b = member[m + 1u].x, c = member[m + 2u].x,
+                   d = member[m + 3u].x;
     below += (a < src ? 1u : 0u) + (b < src ? 1u : 0u) + (c < src ? 1u : 0u) + (d < src ? 1u : 0u);
   }
-  for (; m < c1; ++m) below += member[m] < src ? 1u : 0u;
+  for (; m < c1; ++m) below += member[m].x < src ? 1u : 0u;
   return (int64_t)c0 + below;
 }
 

@@ -317,7 +317,7 @@ hipError_t launch_floating(const KParams& kp, int64_t n, int phase, const double
                            const float* ace, void* ws, hipStream_t st) {
   const WsLayout L = ws_layout(n);
   uint32_t* err = &ws_ptr<WsHeader>(ws, L.err)->err;
-  uint32_t* map = ws_ptr<uint32_t>(ws, L.keyB);
+  uint32_t* map = ws_ptr<uint32_t>(ws, L.member);
   double* part = ws_ptr<double>(ws, L.fpart);
   BodyMotion* motion = ws_ptr<BodyMotion>(ws, L.fmotion);
   // the predictor's moves count towards the displacement since the binning

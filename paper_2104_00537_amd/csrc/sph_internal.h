@@ -159,8 +159,9 @@ constexpr int64_t kLanesMaxN = 131072;
 // Workspace layout (offsets in bytes, each region 256-aligned).
 struct WsLayout {
   size_t err;        // the WsHeader (offset 0)
-  size_t keyA, rank, keyB;   // uint32 [n] each: keys by input index, rank of a
-                             // particle in its cell as counted, cells' members
+  size_t keyA, rank;   // uint32 [n] each: keys by input index, rank of a particle
+                       // in its cell as counted
+  size_t member;       // uint2 [n]: the cells' members, {input index, key}
   size_t xcount;     // uint32 [n / 64]: excluded particles per wavefront, then their offsets
   size_t scan_part;  // uint32 [kScanBlocks]: sums of the scan's chunks
   size_t view_pr;    // float4 [n]: cell-relative position, signed density
@@ -185,7 +186,7 @@ inline WsLayout ws_layout(int64_t n) {
   L.err = off; off = align_up(off + sizeof(WsHeader));
   L.keyA = off; off = align_up(off + 4 * nn);
   L.rank = off; off = align_up(off + 4 * nn);
-  L.keyB = off; off = align_up(off + 4 * nn);
+  L.member = off; off = align_up(off + 8 * nn);
   L.xcount = off; off = align_up(off + 4 * ((nn + 63) / 64));
   L.scan_part = off; off = align_up(off + 4 * (size_t)kScanBlocks);
   // the views carry kViewPad spare entries: the interaction reads candidates
