@@ -128,11 +128,10 @@ enum {
    * (else SPH_E_ARG), so that the longer walk meets no cell twice. */
   SPH_INTERACT_REUSE_CELLS = 8u,
   /* One lane per target particle.  By default a case too small to fill the
-   * GPU (at most 131,072 particles) with the default formulation (Wendland
-   * kernel, artificial viscosity, ddt 0 or 1, no floating bodies or periodic
-   * components) deals each target's neighbour rows to four lanes and sums
-   * their results, which shortens each lane's chain of dependent loads;
-   * results agree up to the order of the FP32 sums (FP64 counts are
+   * GPU (at most 327,680 particles in 3-D, 122,880 in 2-D) deals each
+   * target's neighbour rows to 2, 4, 8 or 16 lanes, the more the smaller it
+   * is, and sums their results, which shortens each lane's chain of dependent
+   * loads; results agree up to the order of the FP32 sums (FP64 counts are
    * identical).  Combines with every other flag. */
   SPH_INTERACT_ONE_LANE = 16u,
   /* The all-FP64 arm of the precision study (Section 5.1): as
@@ -570,7 +569,7 @@ enum {
   SPH_BATCH_WAVE_ALIGNED = 1u,
   /* also an option of sph_batch_describe: in a wave-aligned batch, a slot of
    * at most 131,072 particles gets four lanes per target (as the
-   * single-case pass for a small case), the others one.  The choice depends
+   * single-case pass does for small cases), the others one.  The choice depends
    * on the option and the slot's own size only, so a case's results do not
    * depend on the other slots.  It shortens each target's chain of loads,
    * which pays when the batch is too small to fill the GPU; when it fills

@@ -492,12 +492,12 @@ sph_status sph_batch_describe(const sph_params* params, const int64_t* offsets, 
   bool aligned = true;
   for (int s = 0; s <= n_slots; ++s) aligned = aligned && offsets[s] % 64 == 0;
   // interaction lanes: with SPH_BATCH_FOUR_LANES and wave-aligned slots,
-  // four per target for a slot of at most kLanesMaxN particles (by its own
+  // four per target for a slot of at most kBatchLanesMaxN particles (by its own
   // size only), else one
   const bool four = aligned && (options & SPH_BATCH_FOUR_LANES);
   int64_t lanes = 0;
   for (int s = 0; s < n_slots; ++s) {
-    tab[s].lpt = four && tab[s].n <= kLanesMaxN ? kMaxLanes : 1;
+    tab[s].lpt = four && tab[s].n <= kBatchLanesMaxN ? kBatchLanes : 1;
     tab[s].loff = lanes;
     lanes += tab[s].n * tab[s].lpt;
   }

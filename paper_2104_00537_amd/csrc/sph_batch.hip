@@ -230,12 +230,12 @@ __global__ __launch_bounds__(kBlock) void k_batch_interact(
     if (rs >= 0) {
       const int lpt = __builtin_amdgcn_readfirstlane(tab[rs].lpt);
       const int64_t u = t - tab[rs].loff;
-      if (lpt == kMaxLanes) {
-        a = tab[rs].off + u / kMaxLanes;
-        batch_slot_pass<R, STALE, GEN, PER, kMaxLanes>(tab, rs, 0, t < lanes, n, a, pr, vp, key,
+      if (lpt == kBatchLanes) {
+        a = tab[rs].off + u / kBatchLanes;
+        batch_slot_pass<R, STALE, GEN, PER, kBatchLanes>(tab, rs, 0, t < lanes, n, a, pr, vp, key,
                                                   cstart, ace, arho, visc, nbr, disp, err,
                                                   slot_err, fmag, vmx, cnt, cntw, nfl,
-                                                  (int)(u % kMaxLanes));
+                                                  (int)(u % kBatchLanes));
       } else {
         a = tab[rs].off + u;
         batch_slot_pass<R, STALE, GEN, PER>(tab, rs, 0, t < lanes, n, a, pr, vp, key, cstart, ace,

@@ -44,9 +44,9 @@ __device__ __forceinline__ void key_cell(const KParams& kp, uint32_t k, int& cx,
   cz = (int)(rest / (uint32_t)kp.ncy);
 }
 
-// LPT lanes per target particle (sorted order); LPT = 1 is the production
-// kernel of large cases, LPT = 4 deals each target's rows to four lanes for
-// cases too small to fill the GPU.
+// LPT lanes per target particle (sorted order): 1 is the production kernel of
+// large cases; more deal each target's rows to that many lanes, for cases too
+// small to fill the GPU (see lanes_per_target).
 template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT>
 __global__ __launch_bounds__(kBlock) void k_interact_gather(
     KParams kp, int64_t n, const float4* __restrict__ pr, const float4* __restrict__ vp,
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kBlock) void k_interact_gather(
     const uint8_t* __restrict__ type, const double* __restrict__ pos64, float* __restrict__ ace,
     float* __restrict__ arho, float* __restrict__ visc, uint32_t* __restrict__ nbr,
     BlockRed* __restrict__ red, WsHeader* __restrict__ hdr, const uint32_t* __restrict__ disp) {
-  static_assert(LPT == 1 || LPT == 2 || LPT == 4, "lanes per target: 1, 2 or 4");
+  static_assert(LPT >= 1 && LPT <= kMaxLanes && (LPT & (LPT - 1)) == 0, "a power of two");
   const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   const int64_t i = t / LPT;
   const int sub = (int)(t % LPT);
@@ -273,6 +273,24 @@ __global__ __launch_bounds__(kBlock) void k_interact_arm(
   write_block_red<kBlock / 64>(fmag, vmax_out, cnt_out, cnt_wall, nfl, red, hdr);
 }
 
+// Lanes per target for a case of n particles.  One wavefront that walks its
+// targets' rows alone takes about 100 us in 3-D and 17 us in 2-D, whatever
+// the case's size: a chain of dependent loads (ranges, candidates,
+// velocities, row after row).  While wavefronts are too few to hide it,
+// dealing the rows to more lanes shortens the chain; once the GPU is full the
+// extra instructions cost (rows of different lengths in step, the sums over
+// lanes).  The lines lie where measured times cross (us per pass, 1 / 2 / 4 /
+// 8 / 16 lanes; 3-D dam breaks and 2-D dam breaks, one MI355X):
+//   3-D   13k: 104 / 60 / 36 / 23 / 19      25k: 102 / 59 / 36 / 28 / 28
+//         66k: 105 / 64 / 50 / 50 / 55     127k: 121 / 81 / 84 / 89 / 106
+//        223k: 164 / 124 / 144 / 158 / 189  441k: 220 / 234 / 292 / 321 / 387
+//   2-D   14k: 17 / 12 / 9.7 / 9.6 / 10     54k: 18 / 14 / 15 / 16 / 24
+//        185k: 25 / 27 / 33 / 41 / 69
+static int lanes_per_target(int dim, int64_t n) {
+  if (dim == 2) return n <= 32768 ? 4 : n <= 122880 ? 2 : 1;
+  return n <= 24576 ? 16 : n <= 65536 ? 8 : n <= 98304 ? 4 : n <= 327680 ? 2 : 1;
+}
+
 hipError_t launch_interact(const KParams& kp, int64_t n, const sph_state& s, const uint32_t* key,
                            const uint32_t* cell_start, float* ace, float* arho, float* visc,
                            uint32_t* nbr, uint32_t flags, void* ws, hipStream_t st) {
@@ -319,23 +337,37 @@ hipError_t launch_interact_on(const KParams& kp, int64_t n, const sph_state& s,
   const bool eqm = kp.mass_f == kp.mass_b;
   const bool gen = kp.kernel != 0 || kp.viscosity != 0 || kp.ddt == 2 || kp.floating != 0;
   const bool per = kp.periodic != 0;  // periodic cases run the general kernel with PER
-  // small cases of the default formulation: four lanes per target
-  const bool lanes4 = !gen && !per && !(flags & SPH_INTERACT_ONE_LANE) && n <= kLanesMaxN;
-  const unsigned grid4 = (unsigned)((n * kMaxLanes + kBlock - 1) / kBlock);
-#define SPH_LAUNCH(D, RR, G, PP, GG, PE, LP)                                                 \
-  hipLaunchKernelGGL((k_interact_gather<D, RR, G, PP, GG, PE, LP>),                          \
-                     dim3(LP == 1 ? grid : (grid4 > 0 ? grid4 : 1)), dim3(kBlock), 0, st, kp, n, \
-                     pr, vp, key, cell_start, s.type, s.pos, ace, arho, visc, nbr, red, hdr,   \
-                     w.disp)
-#define SPH_LAUNCH_G(D, RR, G, PP)                                       \
-  if (per) SPH_LAUNCH(D, RR, G, PP, true, true, 1);                      \
-  else if (gen) SPH_LAUNCH(D, RR, G, PP, true, false, 1);                \
-  else if (lanes4) SPH_LAUNCH(D, RR, G, PP, false, false, kMaxLanes);    \
-  else SPH_LAUNCH(D, RR, G, PP, false, false, 1)
-#define SPH_LAUNCH_P(D, RR, G) \
-  if (eqm) SPH_LAUNCH_G(D, RR, G, true); else SPH_LAUNCH_G(D, RR, G, false)
-#define SPH_LAUNCH_R(D, RR) \
-  if (diag) SPH_LAUNCH_P(D, RR, true); else SPH_LAUNCH_P(D, RR, false)
+  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n);
+  // the diagnostic count and unequal masses come with one lane or four
+  if ((diag || !eqm) && lanes > 1) lanes = 4;
+#define SPH_LAUNCH(D, RR, G, PP, GG, PE, LP)                                                  \
+  hipLaunchKernelGGL((k_interact_gather<D, RR, G, PP, GG, PE, LP>),                           \
+                     dim3(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u),           \
+                     dim3(kBlock), 0, st, kp, n, pr, vp, key, cell_start, s.type, s.pos, ace, \
+                     arho, visc, nbr, red, hdr, w.disp)
+// the formulation: periodic cases run the general kernel with PER
+#define SPH_LAUNCH_F(D, RR, G, PP, LP)                  \
+  if (per) SPH_LAUNCH(D, RR, G, PP, true, true, LP);    \
+  else if (gen) SPH_LAUNCH(D, RR, G, PP, true, false, LP); \
+  else SPH_LAUNCH(D, RR, G, PP, false, false, LP)
+#define SPH_LAUNCH_1(D, RR, G, PP)                      \
+  if (lanes == 1) { SPH_LAUNCH_F(D, RR, G, PP, 1); }    \
+  else { SPH_LAUNCH_F(D, RR, G, PP, 4); }
+#define SPH_LAUNCH_2(RR)                                         \
+  if (lanes == 1) { SPH_LAUNCH_F(2, RR, false, true, 1); }       \
+  else if (lanes == 2) { SPH_LAUNCH_F(2, RR, false, true, 2); }  \
+  else { SPH_LAUNCH_F(2, RR, false, true, 4); }
+#define SPH_LAUNCH_3(RR)                                         \
+  if (lanes == 1) { SPH_LAUNCH_F(3, RR, false, true, 1); }       \
+  else if (lanes == 2) { SPH_LAUNCH_F(3, RR, false, true, 2); }  \
+  else if (lanes == 4) { SPH_LAUNCH_F(3, RR, false, true, 4); }  \
+  else if (lanes == 8) { SPH_LAUNCH_F(3, RR, false, true, 8); }  \
+  else { SPH_LAUNCH_F(3, RR, false, true, 16); }
+#define SPH_LAUNCH_R(D, RR)                                      \
+  if (diag && eqm) { SPH_LAUNCH_1(D, RR, true, true); }          \
+  else if (diag) { SPH_LAUNCH_1(D, RR, true, false); }           \
+  else if (!eqm) { SPH_LAUNCH_1(D, RR, false, false); }          \
+  else { SPH_LAUNCH_##D(RR); }
   if (kp.dim == 2) {
     if (reach == 1) { SPH_LAUNCH_R(2, 1); }
     else if (reach == 2) { SPH_LAUNCH_R(2, 2); }
@@ -346,8 +378,10 @@ hipError_t launch_interact_on(const KParams& kp, int64_t n, const sph_state& s,
     else { SPH_LAUNCH_R(3, 3); }
   }
 #undef SPH_LAUNCH_R
-#undef SPH_LAUNCH_G
-#undef SPH_LAUNCH_P
+#undef SPH_LAUNCH_3
+#undef SPH_LAUNCH_2
+#undef SPH_LAUNCH_1
+#undef SPH_LAUNCH_F
 #undef SPH_LAUNCH
   return hipGetLastError();
 }

@@ -129,7 +129,7 @@ constexpr int kDispSlots = 64;
 struct SlotEntry {
   KParams kp;
   uint32_t cbase;    // keys of the slot: cbase .. cbase + kp.ncell_total
-  int32_t lpt;       // interaction lanes per target particle (1 or kMaxLanes)
+  int32_t lpt;       // interaction lanes per target particle (1 or kBatchLanes)
   int64_t off;       // first particle of the slot
   int64_t n;         // particles of the slot
   int64_t loff;      // first interaction lane of the slot (lanes in slot order)
@@ -151,10 +151,12 @@ struct SlotMotion {
   double dt, dmove, vmove, pad;
 };
 
-// Most lanes that share one target particle in the interaction, and the
-// largest case that gets them (n * kMaxLanes / 64 wavefronts at most).
-constexpr int kMaxLanes = 4;
-constexpr int64_t kLanesMaxN = 131072;
+// Most lanes that share one target particle in the interaction (see
+// lanes_per_target), and for a slot of a batch (SPH_BATCH_FOUR_LANES) with
+// the largest slot that gets them.
+constexpr int kMaxLanes = 16;
+constexpr int kBatchLanes = 4;
+constexpr int64_t kBatchLanesMaxN = 131072;
 
 // Workspace layout (offsets in bytes, each region 256-aligned).
 struct WsLayout {

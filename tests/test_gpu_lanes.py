@@ -1,0 +1,82 @@
+"""Lanes per target by the case's size: every number of lanes that the
+interaction deals a target's rows to gives the pairs of one lane per target
+(SPH_INTERACT_ONE_LANE) and sums equal up to their order, in the default
+formulation, with options, on periodic components, and on reused cells.
+Sums of at most ~400 FP32 terms in two orders differ by at most a few times
+sqrt(400) 2^-24 of their largest partial sum, ~1e-6: the bar is 1e-5 of the
+largest value."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2104_00537_amd import cases
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2104_00537_amd import sph as S
+
+DEV = "cuda:0"
+
+# (dim, block, lanes of the default launch)
+SIZES = [(3, (15, 14, 9), 16), (3, (34, 32, 26), 8), (3, (48, 40, 36), 4), (3, (60, 60, 50), 2),
+         (2, (60, 31), 4), (2, (260, 200), 2)]
+OPTIONS = {"default": {}, "options": dict(kernel=1, viscosity=1, visc_nu=1e-2, ddt=2),
+           "unequal": dict(mass_bound_factor=1.25), "periodic": None}
+
+
+def _case(dim, shape, option):
+    rng = np.random.default_rng(sum(shape))
+    if option == "periodic":
+        c = cases.periodic_box(dim, shape=shape, periodic=(0,) if dim == 2 else (0, 1),
+                               cell_div=2, x_sub=2, seed=3)
+    else:
+        c = cases.block_case(dim, shape, walls=True, cell_div=2, x_sub=4, seed=3)
+        kw = dict(OPTIONS[option])
+        f = kw.pop("mass_bound_factor", 1.0)
+        c.params = dataclasses.replace(c.params, mass_bound=c.params.mass_bound * f, **kw)
+    c.pos += rng.uniform(-0.15, 0.15, c.pos.shape) * c.params.dp * (c.type == 0)
+    c.vel[:] = rng.uniform(-0.3, 0.3, c.vel.shape).astype(np.float32)
+    c.rho[:] = (c.rho * (1 + rng.uniform(-1e-3, 1e-3, c.n))).astype(np.float32)
+    return c
+
+
+@pytest.mark.parametrize("option", list(OPTIONS))
+@pytest.mark.parametrize("dim,shape,lanes", SIZES)
+def test_lanes_agree_with_one(dim, shape, lanes, option):
+    c = _case(dim, shape, option)
+    n, P = c.n, S.make_params(c.params)
+    print("lanes", dim, shape, lanes, option, "n", n, flush=True)
+    lo, hi = {(3, 16): (0, 24576), (3, 8): (24576, 65536), (3, 4): (65536, 98304),
+              (3, 2): (98304, 327680), (2, 4): (0, 32768), (2, 2): (32768, 122880)}[(dim, lanes)]
+    assert lo < n <= hi
+    src, dst = S.DeviceState.from_case(c, DEV), S.DeviceState.empty(dim, n, DEV)
+    key, perm = (torch.empty(n, dtype=torch.int32, device=DEV) for _ in range(2))
+    start = torch.empty(c.params.ncell_total() + 1, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+    S.sph_bin_cells(P, n, src, dst, key, perm, start, ws)
+    t, dt = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+    saved = S.DeviceState.empty(dim, n, DEV, with_type=False, with_id=False)
+    for reuse in (0, S.SPH_INTERACT_REUSE_CELLS):
+        out = []
+        for one in (0, S.SPH_INTERACT_ONE_LANE):
+            ace = torch.full((dim, n), float("nan"), device=DEV)
+            arho, visc = (torch.full((n,), float("nan"), device=DEV) for _ in range(2))
+            nbr = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+            inter = torch.zeros(2, dtype=torch.int64, device=DEV)
+            S.sph_interact(P, n, dst, key, start, ace, arho, ws, visc=visc, nbr=nbr,
+                           flags=reuse | one)
+            S.sph_reduce_dt(P, n, dt, ws, interactions=inter)
+            out.append((ace, arho, visc, nbr, inter, dt.clone()))
+        many, single = out
+        assert torch.equal(many[3], single[3]) and torch.equal(many[4], single[4])
+        for k in range(3):
+            scale = max(single[k].abs().max().item(), 1e-30)
+            assert (many[k] - single[k]).abs().max().item() <= 1e-5 * scale
+        assert abs(many[5].item() - single[5].item()) <= 1e-5 * single[5].item()
+        if not reuse:
+            S.sph_symplectic_step(P, n, 0, dt, t, saved, dst, single[0], single[1], ws)
+            S.sph_refresh_view(P, n, dst, key, ws)
+    assert S.sph_read_error(ws) == 0
