@@ -1,12 +1,13 @@
 // Modified dynamic boundary condition (Section 2.6.2 of the DualSPHysics
 // v5.0 paper, Eq. 38-39): wall densities and velocities from ghost nodes.
 //
-// A first kernel lists the wall particles; then one lane per listed wall.  Its ghost node G = r_B +
-// normal_B is binned like a particle; the rows of G's neighbour cells are
-// walked as in the interaction (one range per row, cut to the support sphere
-// of G), candidates are screened in FP32 on the view's offsets with a margin,
-// and the pairs that pass are tested and summed in FP64 on the FP64
-// positions.  The (d+1) x (d+1) corrected system is
+// A first kernel lists the wall particles; then kMdbcLanes lanes per listed
+// wall.  Its ghost node G = r_B + normal_B is binned like a particle; the rows
+// of G's neighbour cells are dealt to the wall's lanes and walked as in the
+// interaction (one range per row, cut to the support sphere of G), candidates
+// are screened in FP32 on the view's offsets with a margin, and the pairs
+// that pass are tested and summed in FP64 on the FP64 positions.  The lanes'
+// sums are added by shuffles, and the (d+1) x (d+1) corrected system is
 // solved by Gaussian elimination with partial pivoting in registers.  Only
 // wall entries of the state density and of the interaction view are written;
 // the fluid entries that the walk reads are never changed, and the sign of a
@@ -16,6 +17,35 @@
 #include "sph_kernels.h"
 
 namespace sph {
+
+// Lanes per wall.  Walls are a part of the particles (145k of 442k in a 3-D
+// dam break: 2270 wavefronts with one lane each, two per SIMD), so their
+// pass is bound by the latency of its loads and not by FP64 arithmetic
+// (vector units 0.3 busy).  At that size k_mdbc takes 292, 203, 194 and
+// 204 us with 1, 2, 4 and 8 lanes, and 184 us with 4 and registers held to
+// 128 for a fourth wavefront per SIMD (280 us with one lane and full-range
+// FP64 division and square root).
+constexpr int kMdbcLanes = 4;
+
+// 1/a (a > 0, infinity included; no denormals) and sqrt(a) (a >= 0, finite;
+// below 1e-290 taken as 0) to about one ulp by Newton steps from the
+// hardware's approximations: without the scaling and the special cases of the
+// full versions, which take most of their instructions.
+__device__ inline double rcp64(double a) {
+  const double y = __builtin_amdgcn_rcp(a);
+  const double x = fma(y, fma(-a, y, 1.0), y);
+  return y > 0.0 ? fma(x, fma(-a, x, 1.0), x) : 0.0;
+}
+__device__ inline double sqrt64(double a) {
+  if (!(a > 1e-290)) return 0.0;
+  const double y = __builtin_amdgcn_rsq(a);
+  double g = a * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, a), h, g);
+  return fma(fma(-g, g, a), h, g);
+}
 
 // Kernel value and gradient factor (grad W = F r) in FP64: Wendland C2
 // (Eq. 11), W = alpha_D (1 - q/2)^4 (2q + 1), F = kfab (1 - q/2)^3, or cubic
@@ -87,28 +117,53 @@ __global__ void k_zero_wall_count(WsHeader* __restrict__ hdr) {
 }
 
 // The wall particles (not excluded) of the sorted state, appended to a work
-// list in any order (one atomic per wave); each wall's result depends only on
-// its own inputs, so the order does not matter.
+// list in any order; each wall's result depends only on its own inputs, so the
+// order does not matter.  A block takes kListRounds rounds of its threads and
+// makes one atomic for all of them (6.9 us for 441k particles): with one per
+// wavefront the atomics on the one counter, about 5 ns each, took 41 us.
+constexpr int kListRounds = 8;
 __global__ __launch_bounds__(kBlock) void k_wall_list(int64_t n, const uint8_t* __restrict__ type,
                                                       uint32_t* __restrict__ list,
                                                       WsHeader* __restrict__ hdr) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool wall = i < n && !is_excluded(type[i]) && !is_fluid(type[i]);
-  const uint64_t mask = __ballot(wall);
-  if (mask == 0ull) return;
-  const int lane = threadIdx.x & 63;
-  const int leader = (int)__builtin_ctzll(mask);
-  uint32_t base = 0;
-  if (lane == leader) base = atomicAdd(&hdr->nwall, (uint32_t)__popcll(mask));
-  base = __shfl(base, leader, 64);
-  if (wall) {
-    const uint64_t below = lane == 0 ? 0ull : (mask & (~0ull >> (64 - lane)));
-    list[base + (uint32_t)__popcll(below)] = (uint32_t)i;
+  constexpr int kWaves = kBlock / 64;
+  __shared__ uint32_t first[kListRounds * kWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i0 = (int64_t)blockIdx.x * (kBlock * kListRounds) + threadIdx.x;
+  uint64_t mask[kListRounds];
+#pragma unroll
+  for (int r = 0; r < kListRounds; ++r) {
+    const int64_t i = i0 + r * kBlock;
+    mask[r] = __ballot(i < n && !is_excluded(type[i]) && !is_fluid(type[i]));
+    if (lane == 0) first[r * kWaves + wave] = (uint32_t)__popcll(mask[r]);
   }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    for (int k = 0; k < kListRounds * kWaves; ++k) {
+      const uint32_t c = first[k];
+      first[k] = total;
+      total += c;
+    }
+    const uint32_t base = total ? atomicAdd(&hdr->nwall, total) : 0u;
+    for (int k = 0; k < kListRounds * kWaves; ++k) first[k] += base;
+  }
+  __syncthreads();
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int r = 0; r < kListRounds; ++r)
+    if ((mask[r] >> lane) & 1ull)
+      list[first[r * kWaves + wave] + (uint32_t)__popcll(mask[r] & below)] =
+          (uint32_t)(i0 + r * kBlock);
+}
+
+// The sum of v over the kMdbcLanes adjacent lanes of a wall, in every lane.
+__device__ inline double lanes_sum(double v) {
+  for (int off = 1; off < kMdbcLanes; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
 }
 
 template <int DIM, int R>
-__global__ __launch_bounds__(kBlock) void k_mdbc(KParams kp, int64_t n, sph_state s,
+__global__ __launch_bounds__(kBlock, 4) void k_mdbc(KParams kp, int64_t n, sph_state s,
                                                  const uint32_t* __restrict__ cstart,
                                                  float4* __restrict__ pr,
                                                  float4* __restrict__ vp,
@@ -116,8 +171,9 @@ __global__ __launch_bounds__(kBlock) void k_mdbc(KParams kp, int64_t n, sph_stat
                                                  const WsHeader* __restrict__ hdr) {
   constexpr int M = DIM + 1;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)hdr->nwall) return;
-  const int64_t i = list[t];
+  const int sub = (int)(t % kMdbcLanes);
+  if (t / kMdbcLanes >= (int64_t)hdr->nwall) return;  // (all lanes of a wall together)
+  const int64_t i = list[t / kMdbcLanes];
   double g[3] = {0.0, 0.0, 0.0}, rb[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
@@ -138,9 +194,11 @@ __global__ __launch_bounds__(kBlock) void k_mdbc(KParams kp, int64_t n, sph_stat
   }
   // sums of the corrected system: sw = sum V w, swr = sum V w r,
   // sfr = sum V F r, sfrr = sum V F r r^T (symmetric, upper part), b0 =
-  // sum m w, bf = sum m F r; and the Shepard velocity sum
+  // sum m w, bf = sum m F r (m is applied after the sums); and the Shepard
+  // velocity sum
   double sw = 0.0, swr[3] = {0.0, 0.0, 0.0}, sfr[3] = {0.0, 0.0, 0.0};
   double sfrr[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  const double mb = kp.mass_f;
   double b0 = 0.0, bf[3] = {0.0, 0.0, 0.0}, sv[3] = {0.0, 0.0, 0.0};
   // the ghost node in the view's frame: fixed-point x (as the reorder writes
   // it), y and z relative to the ghost's cell
@@ -158,13 +216,15 @@ __global__ __launch_bounds__(kBlock) void k_mdbc(KParams kp, int64_t n, sph_stat
   const int reach = R * kp.x_sub;
   const int xlo = c[0] - reach < 0 ? 0 : c[0] - reach;
   const int xhi = c[0] + reach >= kp.ncx ? kp.ncx - 1 : c[0] + reach;
-  const int zlo = DIM == 3 ? -R : 0, zhi = DIM == 3 ? R : 0;
-  for (int dz = zlo; dz <= (inside ? zhi : zlo - 1); ++dz) {
+  constexpr int kRowsY = 2 * R + 1;
+  constexpr int kRows = kRowsY * (DIM == 3 ? 2 * R + 1 : 1);
+  for (int q = sub; q < (inside ? kRows : 0); q += kMdbcLanes) {
+    const int dz = (DIM == 3 ? -R : 0) + q / kRowsY, dy = q % kRowsY - R;
     const int z = c[2] + dz;
     if (z < 0 || z >= kp.ncz) continue;
     const float ez0 = (float)dz * cs - zg;
     const float ez = DIM == 3 ? (dz > 0 ? ez0 : (dz < 0 ? -(ez0 + cs) : 0.f)) : 0.f;
-    for (int dy = -R; dy <= R; ++dy) {
+    {
       const int y = c[1] + dy;
       if (y < 0 || y >= kp.ncy) continue;
       const float ey0 = (float)dy * cs - yg;
@@ -214,17 +274,16 @@ __global__ __launch_bounds__(kBlock) void k_mdbc(KParams kp, int64_t n, sph_stat
           }
           if (!(r2 < kp.support2)) continue;
           double w, f;
-          kernel_wf64(kp, sqrt(r2), w, f);
-          const double mb = kp.mass_f;
-          const double vb = mb / (double)pb[u].w;
+          kernel_wf64(kp, sqrt64(r2), w, f);
+          const double vb = mb * rcp64((double)pb[u].w);
           const double vw = vb * w, vf = vb * f;
           sw += vw;
-          b0 += mb * w;
+          b0 += w;
 #pragma unroll
           for (int a = 0; a < DIM; ++a) {
             swr[a] += vw * r[a];
             sfr[a] += vf * r[a];
-            bf[a] += mb * f * r[a];
+            bf[a] += f * r[a];
           }
           sfrr[0] += vf * r[0] * r[0];
           sfrr[1] += vf * r[0] * r[1];
@@ -241,6 +300,19 @@ __global__ __launch_bounds__(kBlock) void k_mdbc(KParams kp, int64_t n, sph_stat
       }
     }
   }
+  sw = lanes_sum(sw);
+  b0 = mb * lanes_sum(b0);
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) {
+    swr[a] = lanes_sum(swr[a]);
+    sfr[a] = lanes_sum(sfr[a]);
+    bf[a] = mb * lanes_sum(bf[a]);
+    sv[a] = lanes_sum(sv[a]);
+  }
+#pragma unroll
+  for (int a = 0; a < 6; ++a)
+    if (DIM == 3 || a == 0 || a == 1 || a == 3) sfrr[a] = lanes_sum(sfrr[a]);
+  if (sub != 0) return;
   double rho_b = kp.rho0;
   double vout[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -287,9 +359,12 @@ hipError_t launch_mdbc(const KParams& kp, int64_t n, const sph_state& s, const u
   // the work list lives in the sort's key buffer, free once the cells are
   // binned (sph_bin_cells must not run between this and the next launch)
   uint32_t* list = ws_ptr<uint32_t>(ws, L.keyA);
-  const unsigned grid = (unsigned)((n + kBlock - 1) / kBlock);
+  // (room for every particle being a wall; blocks past the list leave at once)
+  const unsigned grid = (unsigned)((n * kMdbcLanes + kBlock - 1) / kBlock);
+  const int64_t chunk = kBlock * kListRounds;
   hipLaunchKernelGGL(k_zero_wall_count, dim3(1), dim3(64), 0, st, hdr);
-  hipLaunchKernelGGL(k_wall_list, dim3(grid), dim3(kBlock), 0, st, n, s.type, list, hdr);
+  hipLaunchKernelGGL(k_wall_list, dim3((unsigned)((n + chunk - 1) / chunk)), dim3(kBlock), 0, st,
+                     n, s.type, list, hdr);
 #define SPH_MDBC(D, RR)                                                                    \
   hipLaunchKernelGGL((k_mdbc<D, RR>), dim3(grid), dim3(kBlock), 0, st, kp, n, s, cell_start, \
                      pr, vp, list, hdr)
