@@ -17,6 +17,8 @@
  *                        dynamic boundary condition (Eq. 38-39), before a PI.
  *   sph_symplectic_step  SU: symplectic predictor / corrector (Eq. 33-34), with
  *                        imposed motion of moving walls (Eq. 37).
+ *   sph_symplectic_update  sph_reduce_dt, a phase of sph_symplectic_step and
+ *                        (predictor) sph_refresh_view in one call.
  *   sph_floating_step    SU of rigid floating bodies (Section 3.2, Eq. 47-50),
  *                        after each phase of sph_symplectic_step.
  *   sph_shifting         particle shifting (Section 2.8, Eq. 40-41, 53) after
@@ -420,6 +422,20 @@ sph_status sph_symplectic_step(const sph_params* p, int64_t n, int32_t phase,
                                sph_state* s, const float* ace,
                                const float* arho, void* ws, size_t ws_bytes,
                                void* stream);
+
+/* sph_reduce_dt and a phase of sph_symplectic_step in one call, with the same
+ * results in fewer kernels (the step of a case without floating bodies):
+ *   phase 0: *dt and interactions as by sph_reduce_dt, the predictor with
+ *     that dt, and sph_refresh_view of its result (key of the last binning);
+ *   phase 1: *dt_half and interactions as by sph_reduce_dt (the time step of
+ *     the second pass, which no update uses), and the corrector with *dt (key
+ *     is not used).
+ * Not for an all-FP64 state. */
+sph_status sph_symplectic_update(const sph_params* p, int64_t n, int32_t phase, double* dt,
+                                 double* dt_half, uint64_t* interactions, double* t,
+                                 sph_state* saved, sph_state* s, const float* ace,
+                                 const float* arho, const uint32_t* key, void* ws,
+                                 size_t ws_bytes, void* stream);
 
 /* SU, Section 2.5.1: the Verlet scheme, one interaction per step, on the
  * sorted state.

@@ -370,6 +370,22 @@ sph_status sph_symplectic_step(const sph_params* p, int64_t n, int32_t phase, co
                                       (hipStream_t)stream));
 }
 
+sph_status sph_symplectic_update(const sph_params* p, int64_t n, int32_t phase, double* dt,
+                                 double* dt_half, uint64_t* interactions, double* t,
+                                 sph_state* saved, sph_state* s, const float* ace,
+                                 const float* arho, const uint32_t* key, void* ws,
+                                 size_t ws_bytes, void* stream) {
+  if (!params_ok(p) || !n_ok(n) || !dt || !t || !ws) return SPH_E_ARG;
+  if ((phase != 0 && phase != 1) || (phase == 1 && !dt_half)) return SPH_E_ARG;
+  if (n > 0 && (!state_ok(s, true) || !state_ok(saved, false) || !ace || !arho || f64_state(s) ||
+                (phase == 0 && !key)))
+    return SPH_E_ARG;
+  if (ws_bytes < ws_layout(n).total) return SPH_E_WORKSPACE;
+  sph_state sv = n > 0 ? *saved : sph_state{}, st = n > 0 ? *s : sph_state{};
+  return hip_status(launch_update(make_kparams(*p), n, phase, dt, dt_half, interactions, t, sv, st,
+                                  ace, arho, key, ws, (hipStream_t)stream));
+}
+
 sph_status sph_verlet_step(const sph_params* p, int64_t n, int32_t mode, const double* dt,
                            double* t, sph_state* prev, sph_state* s, const float* ace,
                            const float* arho, void* ws, size_t ws_bytes, void* stream) {

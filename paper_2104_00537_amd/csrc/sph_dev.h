@@ -30,15 +30,13 @@ __device__ inline double wrap_coord(const KParams& kp, int k, double x) {
 // they sort last and lie in no cell range.  Periodic components take the
 // wrapped coordinate (and its last cell if the product rounds up to the
 // end).
-__device__ inline uint32_t cell_key_local(const KParams& kp, const double* __restrict__ pos,
-                                          const uint8_t* __restrict__ type, int64_t n,
-                                          int64_t i) {
-  if (is_excluded(type[i])) return kp.ncell_total;
+template <typename X>  // x(k): the coordinate along component k
+__device__ inline uint32_t cell_key_at(const KParams& kp, int dim, X&& x) {
   const double org[3] = {kp.ox, kp.oy, kp.oz};
   const int nc[3] = {kp.ncx, kp.ncy, kp.ncz};
   int c[3] = {0, 0, 0};
-  for (int k = 0; k < kp.dim; ++k) {
-    const double d = __dsub_rn(wrap_coord(kp, k, pos[k * n + i]), org[k]);
+  for (int k = 0; k < dim; ++k) {
+    const double d = __dsub_rn(wrap_coord(kp, k, x(k)), org[k]);
     const double s = __dmul_rn(d, k == 0 ? kp.inv_csx : kp.inv_cs);
     double f = floor(s);
     if (((kp.periodic >> k) & 1) && f == (double)nc[k]) f -= 1.0;
@@ -46,6 +44,12 @@ __device__ inline uint32_t cell_key_local(const KParams& kp, const double* __res
     c[k] = (int)f;
   }
   return (uint32_t)(c[0] + nc[0] * (c[1] + nc[1] * c[2]));
+}
+__device__ inline uint32_t cell_key_local(const KParams& kp, const double* __restrict__ pos,
+                                          const uint8_t* __restrict__ type, int64_t n,
+                                          int64_t i) {
+  if (is_excluded(type[i])) return kp.ncell_total;
+  return cell_key_at(kp, kp.dim, [&](int k) { return pos[k * n + i]; });
 }
 
 // Counts the calling lane's particle in its cell k (lanes that take part, in
@@ -258,6 +262,70 @@ __device__ inline bool symplectic_one(const KParams& kp, int64_t n, int64_t i, d
   }
   const float rf = (float)r;
   s.rho[i] = rf;
+  return bad || !(rf > 0.f) || !isfinite(rf);
+}
+
+// The predictor (symplectic_one<0>) and the view refresh of its result in one
+// pass: the particle's new position, velocity and density go to the state and,
+// from registers, to its view entry, relative to the cell of its key from the
+// last binning.  All loads come before the first store: the state's arrays may
+// alias as far as the compiler knows, so it moves none across.  A particle that
+// leaves the grid along an open component is excluded, as a binning would; its
+// view entry gets NaN offsets and zero density, so it meets no target in the
+// cell range it still sits in (newly is set).
+template <int DIM>
+__device__ inline bool predict_view_one(const KParams& kp, int64_t n, int64_t i, double dt,
+                                        double dmove, double vmove, const sph_state& saved,
+                                        const sph_state& s, const float* __restrict__ ace,
+                                        const float* __restrict__ arho,
+                                        const uint32_t* __restrict__ key,
+                                        float4* __restrict__ pr, float4* __restrict__ vp,
+                                        double& disp2, bool& newly) {
+  double x[3] = {0.0, 0.0, 0.0};
+  float v[3] = {0.f, 0.f, 0.f}, a[3] = {0.f, 0.f, 0.f};
+  const uint8_t t = s.type[i];
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    x[d] = s.pos[d * n + i];
+    v[d] = s.vel[d * n + i];
+    a[d] = ace[d * n + i];
+  }
+  const float rho = s.rho[i], ar = arho[i];
+  const uint32_t lkey = key[i];
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    saved.pos[d * n + i] = x[d];
+    saved.vel[d * n + i] = v[d];
+  }
+  saved.rho[i] = rho;
+  if (is_excluded(t)) return false;  // (its view entry was written by the binning)
+  bool bad = false;
+  if (is_fluid(t)) {
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const double v0 = (double)v[d];
+      const double x0 = x[d], x1 = x0 + 0.5 * dt * v0;
+      s.pos[d * n + i] = x[d] = x1;
+      disp2 += (x1 - x0) * (x1 - x0);
+      s.vel[d * n + i] = v[d] = (float)(v0 + 0.5 * dt * (double)a[d]);
+      bad |= !isfinite(v[d]);
+    }
+  } else if ((t & 0x7f) == SPH_BOUND_MOVING) {
+    s.pos[i] = x[0] = x[0] + dmove;
+    s.vel[i] = v[0] = (float)vmove;
+    disp2 += dmove * dmove;
+  }
+  const float rf = (float)((double)rho + 0.5 * dt * (double)ar);
+  s.rho[i] = rf;
+  if (cell_key_at(kp, DIM, [&](int k) { return x[k]; }) == kp.ncell_total) {
+    s.type[i] = t | SPH_EXCLUDED;
+    newly = true;
+    const float nan = __builtin_nanf("");
+    pr[i] = make_float4(0.f, nan, nan, 0.f);
+    vp[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  } else {
+    write_view(kp, i, x, v, rf, t, lkey, pr, vp);
+  }
   return bad || !(rf > 0.f) || !isfinite(rf);
 }
 

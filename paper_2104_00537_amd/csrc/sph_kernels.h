@@ -58,6 +58,10 @@ hipError_t launch_interact_list(const KParams& kp, int64_t n, const sph_state& s
                                 hipStream_t st);
 hipError_t launch_reduce_dt(const KParams& kp, int64_t n, double* dt, uint64_t* interactions,
                             float* maxima, void* ws, hipStream_t st);
+hipError_t launch_update(const KParams& kp, int64_t n, int phase, double* dt, double* dt_half,
+                         uint64_t* interactions, double* t, sph_state& saved, sph_state& s,
+                         const float* ace, const float* arho, const uint32_t* key, void* ws,
+                         hipStream_t st);
 hipError_t launch_symplectic(const KParams& kp, int64_t n, int phase, const double* dt, double* t,
                              sph_state& saved, sph_state& s, const float* ace, const float* arho,
                              void* ws, hipStream_t st);

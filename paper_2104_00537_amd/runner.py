@@ -232,14 +232,21 @@ class Simulation:
         else:
             call("interact", S.sph_interact, P, n, b, self.key, self.cell_start, self.ace,
                  self.arho, self.ws, flags=self.flags, stream=stream)
-        call("reduce_dt", S.sph_reduce_dt, P, n, self.dt, self.ws,
-             interactions=self.interactions, stream=stream)
-        call("symplectic", S.sph_symplectic_step, P, n, 0, self.dt, self.t, s0, b, self.ace,
-             self.arho, self.ws, stream=stream)
-        if self.bodies is not None:
-            call("floating", S.sph_floating_step, P, n, 0, self.dt, self.bodies, s0, b, self.ace,
-                 self.ws, stream=stream)
-        call("refresh_view", S.sph_refresh_view, P, n, b, self.key, self.ws, stream=stream)
+        # dt, update and refresh in one call, unless each is timed by itself or
+        # the floating bodies' step comes between them
+        fused = timing is None and self.bodies is None
+        if fused:
+            S.sph_symplectic_update(P, n, 0, self.dt, self.dt_half, self.interactions, self.t, s0,
+                                    b, self.ace, self.arho, self.key, self.ws, stream=stream)
+        else:
+            call("reduce_dt", S.sph_reduce_dt, P, n, self.dt, self.ws,
+                 interactions=self.interactions, stream=stream)
+            call("symplectic", S.sph_symplectic_step, P, n, 0, self.dt, self.t, s0, b, self.ace,
+                 self.arho, self.ws, stream=stream)
+            if self.bodies is not None:
+                call("floating", S.sph_floating_step, P, n, 0, self.dt, self.bodies, s0, b, self.ace,
+                     self.ws, stream=stream)
+            call("refresh_view", S.sph_refresh_view, P, n, b, self.key, self.ws, stream=stream)
         if self.neighbour_list:
             call("interact", S.sph_interact_list, P, n, b, self.key, self.cell_start, self.list,
                  self.ace, self.arho, self.ws, flags=self.flags | S.SPH_INTERACT_REUSE_CELLS,
@@ -248,13 +255,17 @@ class Simulation:
             call("interact", S.sph_interact, P, n, b, self.key, self.cell_start, self.ace,
                  self.arho, self.ws, flags=self.flags | S.SPH_INTERACT_REUSE_CELLS,
                  stream=stream)
-        call("reduce_dt", S.sph_reduce_dt, P, n, self.dt_half, self.ws,
-             interactions=self.interactions, stream=stream)
-        call("symplectic", S.sph_symplectic_step, P, n, 1, self.dt, self.t, s0, b, self.ace,
-             self.arho, self.ws, stream=stream)
-        if self.bodies is not None:
-            call("floating", S.sph_floating_step, P, n, 1, self.dt, self.bodies, s0, b, self.ace,
-                 self.ws, stream=stream)
+        if fused:
+            S.sph_symplectic_update(P, n, 1, self.dt, self.dt_half, self.interactions, self.t, s0,
+                                    b, self.ace, self.arho, self.key, self.ws, stream=stream)
+        else:
+            call("reduce_dt", S.sph_reduce_dt, P, n, self.dt_half, self.ws,
+                 interactions=self.interactions, stream=stream)
+            call("symplectic", S.sph_symplectic_step, P, n, 1, self.dt, self.t, s0, b, self.ace,
+                 self.arho, self.ws, stream=stream)
+            if self.bodies is not None:
+                call("floating", S.sph_floating_step, P, n, 1, self.dt, self.bodies, s0, b, self.ace,
+                     self.ws, stream=stream)
         if self.shifting:
             call("shifting", S.sph_shifting, P, n, b, self.key, self.cell_start, self.dt, self.ws,
                  flags=S.SPH_INTERACT_REUSE_CELLS, stream=stream)

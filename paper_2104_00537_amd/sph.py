@@ -35,7 +35,7 @@ SPH_INTERACT_F64_STATE = 32
 EXPORTS = ("sph_workspace_bytes", "sph_bin_cells", "sph_refresh_view", "sph_interact",
            "sph_interact_noalloc", "sph_list_bytes", "sph_build_list", "sph_interact_list",
            "sph_list_walks", "sph_reduce_dt",
-           "sph_symplectic_step", "sph_verlet_step", "sph_mdbc", "sph_floating_step",
+           "sph_symplectic_step", "sph_symplectic_update", "sph_verlet_step", "sph_mdbc", "sph_floating_step",
            "sph_shifting",
            "sph_read_error", "sph_clear_error", "sph_strerror",
            "sph_batch_table_bytes", "sph_batch_describe", "sph_batch_workspace_bytes",
@@ -127,6 +127,9 @@ def _load() -> C.CDLL:
     L.sph_symplectic_step.restype = C.c_int32
     L.sph_symplectic_step.argtypes = [P(SphParams), C.c_int64, C.c_int32, VP, VP,
                                       P(SphState), P(SphState), VP, VP, VP, C.c_size_t, VP]
+    L.sph_symplectic_update.restype = C.c_int32
+    L.sph_symplectic_update.argtypes = [P(SphParams), C.c_int64, C.c_int32, VP, VP, VP, VP,
+                                        P(SphState), P(SphState), VP, VP, VP, VP, C.c_size_t, VP]
     L.sph_verlet_step.restype = C.c_int32
     L.sph_verlet_step.argtypes = [P(SphParams), C.c_int64, C.c_int32, VP, VP,
                                   P(SphState), P(SphState), VP, VP, VP, C.c_size_t, VP]
@@ -355,6 +358,16 @@ def sph_symplectic_step(params: SphParams, n: int, phase: int, dt: torch.Tensor,
     _check(lib.sph_symplectic_step(C.byref(params), int(n), int(phase), _ptr(dt), _ptr(t),
                                    C.byref(saved.c()), C.byref(s.c()), _ptr(ace), _ptr(arho),
                                    _ptr(ws), ws.numel(), _stream(stream)), "sph_symplectic_step")
+
+
+def sph_symplectic_update(params: SphParams, n: int, phase: int, dt: torch.Tensor,
+                          dt_half: torch.Tensor, interactions: Optional[torch.Tensor],
+                          t: torch.Tensor, saved: DeviceState, s: DeviceState, ace: torch.Tensor,
+                          arho: torch.Tensor, key: torch.Tensor, ws: torch.Tensor, stream=None):
+    _check(lib.sph_symplectic_update(C.byref(params), int(n), int(phase), _ptr(dt), _ptr(dt_half),
+                                     _ptr(interactions), _ptr(t), C.byref(saved.c()),
+                                     C.byref(s.c()), _ptr(ace), _ptr(arho), _ptr(key), _ptr(ws),
+                                     ws.numel(), _stream(stream)), "sph_symplectic_update")
 
 
 def sph_verlet_step(params: SphParams, n: int, mode: int, dt: torch.Tensor, t: torch.Tensor,

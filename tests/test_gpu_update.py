@@ -1,0 +1,110 @@
+"""The one-call update (time step, predictor or corrector, view refresh) against
+the separate calls it stands for, at sizes around a block, with fixed and moving
+walls, particles that leave the grid and a case above the size up to which
+every block sums the partial results itself.
+
+The same FP64 expressions are evaluated on both sides: whole numbers and the
+time step must be equal, positions may differ by one rounding of FP64 and
+velocities and densities by one of FP32 where a compiler fuses differently."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2104_00537_amd import cases
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2104_00537_amd import sph as S
+
+DEV = "cuda:0"
+
+
+def _case(kind):
+    if kind == "moving":
+        c = cases.sloshing_3d(dp=0.05, seed=3, cell_div=2, x_sub=4)
+        assert c.params.motion_omega != 0.0
+    elif kind == "2d":
+        c = cases.dam_break_2d(cell_div=2, x_sub=4)
+    elif kind == "large":
+        c = cases.block_case(3, (70, 66, 62), walls=False, cell_div=2, x_sub=2, seed=5)
+    else:
+        c = cases.block_case(3, (15, 14, 9), walls=True, cell_div=2, x_sub=4, seed=5)
+    rng = np.random.default_rng(11)
+    fluid = c.type == cases.FLUID
+    c.vel[:, fluid] += rng.uniform(-0.3, 0.3, (c.params.dim, fluid.sum())).astype(np.float32)
+    if kind == "leaving":  # three particles below the grid's upper end, on their way out
+        out = np.flatnonzero(fluid)[:3]
+        cp = c.params
+        c.pos[-1, out] = cp.origin[-1] + cp.ncell[-1] * cp.cell_size - 1e-9 * cp.dp
+        c.vel[-1, out] = np.float32(1.0)
+    return c
+
+
+def _run(c, n, fused):
+    """Binning, then two half steps with an interaction before each."""
+    cp = c.params
+    P = S.make_params(cp)
+    src = S.DeviceState.from_case(c, DEV)
+    b = S.DeviceState.empty(cp.dim, n, DEV)
+    saved = S.DeviceState.empty(cp.dim, n, DEV)
+    key = torch.empty(n, dtype=torch.int32, device=DEV)
+    perm = torch.empty_like(key)
+    start = torch.empty(cp.ncell_total() + 1, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+    ace = torch.zeros((cp.dim, n), dtype=torch.float32, device=DEV)
+    arho = torch.zeros(n, dtype=torch.float32, device=DEV)
+    nbr = torch.zeros(n, dtype=torch.int32, device=DEV)
+    dt, dth = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+    t = torch.full((1,), 0.37, dtype=torch.float64, device=DEV)
+    inter = torch.zeros(2, dtype=torch.int64, device=DEV)
+    S.sph_bin_cells(P, n, src, b, key, perm, start, ws)
+    S.sph_interact(P, n, b, key, start, ace, arho, ws)
+    if fused:
+        S.sph_symplectic_update(P, n, 0, dt, dth, inter, t, saved, b, ace, arho, key, ws)
+    else:
+        S.sph_reduce_dt(P, n, dt, ws, interactions=inter)
+        S.sph_symplectic_step(P, n, 0, dt, t, saved, b, ace, arho, ws)
+        S.sph_refresh_view(P, n, b, key, ws)
+    S.sph_interact(P, n, b, key, start, ace, arho, ws, nbr=nbr, flags=S.SPH_INTERACT_REUSE_CELLS)
+    half = [x.cpu().numpy().copy() for x in (b.pos, b.vel, b.rho, b.type, saved.pos, saved.vel,
+                                             saved.rho, ace, arho, nbr)]
+    if fused:
+        S.sph_symplectic_update(P, n, 1, dt, dth, inter, t, saved, b, ace, arho, key, ws)
+    else:
+        S.sph_reduce_dt(P, n, dth, ws, interactions=inter)
+        S.sph_symplectic_step(P, n, 1, dt, t, saved, b, ace, arho, ws)
+    torch.cuda.synchronize()
+    full = [x.cpu().numpy().copy() for x in (b.pos, b.vel, b.rho, b.type)]
+    return half, full, (dt.item(), dth.item(), t.item(), inter.tolist(), S.sph_read_error(ws))
+
+
+@pytest.mark.parametrize("kind,n", [("fixed", None), ("fixed", 1), ("fixed", 256), ("fixed", 257),
+                                    ("moving", None), ("2d", None), ("leaving", None),
+                                    ("large", None)])
+def test_one_call_matches_the_separate_calls(kind, n):
+    c = _case(kind)
+    if n is not None:
+        sel = np.random.default_rng(n).permutation(c.n)[:n]
+        c = cases.Case(c.params, np.ascontiguousarray(c.pos[:, sel]),
+                       np.ascontiguousarray(c.vel[:, sel]), c.rho[sel].copy(), c.type[sel].copy(),
+                       dict(c.meta))
+    if kind == "large":
+        assert c.n > 262144
+    ha, fa, sa = _run(c, c.n, False)
+    hb, fb, sb = _run(c, c.n, True)
+    assert sa[0] == sb[0] and sa[2:] == sb[2:]
+    assert sa[1] == pytest.approx(sb[1], rel=1e-5)
+    if kind == "leaving":
+        assert np.count_nonzero(hb[3] & 0x80) == 3 and sb[4] != 0
+    for a, b, tol in zip(ha + fa, hb + fb, [4e-16, 2e-7, 2e-7, 0, 0, 0, 0, 1e-5, 1e-5, 0,
+                                            4e-16, 1e-5, 2e-7, 0]):
+        assert a.dtype == b.dtype
+        ok = np.isfinite(a)
+        assert np.array_equal(ok, np.isfinite(b))
+        if ok.any():
+            scale = np.abs(a[ok].astype(np.float64)).max()
+            err = np.abs(a[ok].astype(np.float64) - b[ok].astype(np.float64)).max()
+            assert err <= tol * scale, (kind, tol, err, scale)
