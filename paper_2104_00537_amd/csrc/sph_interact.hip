@@ -1,8 +1,9 @@
 // Particle interaction (Section 2.3 of the DualSPHysics v5.0 paper): the
 // continuity and momentum sums over neighbours within 2h, on gfx950.
 //
-// One lane per target particle in sorted order walks the rows of its
-// neighbour cells (gather_walk).  Blocks cover consecutive targets and are
+// One lane per target particle in sorted order (a few where the case is too
+// small to fill the GPU) walks the rows of its neighbour cells (sph_gather.h,
+// gather_walk).  Blocks cover consecutive targets and are
 // dealt to the XCDs in chunks of 16 consecutive blocks (xcd_block): the blocks
 // of a chunk share neighbour views through their XCD's L2, and every XCD gets
 // chunks from every part of the domain, which balances the work across the
@@ -10,132 +11,9 @@
 // deterministic.
 #include <type_traits>
 
-#include "sph_kernels.h"
-#include "sph_dev.h"
-#include "sph_pair.h"
+#include "sph_gather.h"
 
 namespace sph {
-
-// ------------------------------------------------- interaction: gather --
-// The target's own terms from its view entry (sorted slot i).
-template <bool GEN>
-__device__ __forceinline__ void target_data(const KParams& kp, int64_t i,
-                                            const float4* __restrict__ pr,
-                                            const float4* __restrict__ vp,
-                                            const uint8_t* __restrict__ type, TargetData& T) {
-  const float4 pa = pr[i], va = vp[i];
-  T.fluid = pa.w > 0.f;
-  T.rho = fabsf(pa.w);
-  T.irho = __builtin_amdgcn_rcpf(T.rho);
-  T.ik = kp.kvc_f * T.irho;
-  T.p = va.w;
-  T.vx = va.x;
-  T.vy = va.y;
-  T.vz = va.z;
-  T.flt = GEN && kp.floating && is_floating(type[i]);
-}
-
-// Cell coordinates (in key cells) of key k.
-__device__ __forceinline__ void key_cell(const KParams& kp, uint32_t k, int& cx, int& cy,
-                                         int& cz) {
-  cx = (int)(k % (uint32_t)kp.ncx);
-  const uint32_t rest = k / (uint32_t)kp.ncx;
-  cy = (int)(rest % (uint32_t)kp.ncy);
-  cz = (int)(rest / (uint32_t)kp.ncy);
-}
-
-// LPT lanes per target particle (sorted order): 1 is the production kernel of
-// large cases; more deal each target's rows to that many lanes, for cases too
-// small to fill the GPU (see lanes_per_target).
-template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT>
-__global__ __launch_bounds__(kBlock) void k_interact_gather(
-    KParams kp, int64_t n, const float4* __restrict__ pr, const float4* __restrict__ vp,
-    const uint32_t* __restrict__ key, const uint32_t* __restrict__ cstart,
-    const uint8_t* __restrict__ type, const double* __restrict__ pos64, float* __restrict__ ace,
-    float* __restrict__ arho, float* __restrict__ visc, uint32_t* __restrict__ nbr,
-    BlockRed* __restrict__ red, WsHeader* __restrict__ hdr, const uint32_t* __restrict__ disp) {
-  static_assert(LPT >= 1 && LPT <= kMaxLanes && (LPT & (LPT - 1)) == 0, "a power of two");
-  const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-  const int64_t i = t / LPT;
-  const int sub = (int)(t % LPT);
-  float fmag = 0.f, vmax_out = 0.f;
-  uint32_t cnt_out = 0, cnt_wall = 0, nfl = 0;
-  // cells reused after a view refresh (R above the cells' own stencil): cull
-  // with the support widened by the largest displacement since the binning
-  float cull2 = kp.support2_f * 1.0002f;
-  if (R > kp.cell_div) {
-    const float delta = read_displacement(disp);
-    const float rc = __builtin_amdgcn_sqrtf(kp.support2_f) * 1.0001f + delta;
-    cull2 = rc * rc;
-    if (!(2.f * delta < kp.cs_f) && blockIdx.x == 0 && threadIdx.x == 0)
-      set_error(&hdr->err, SPH_ERR_MARGIN);
-  } else if (blockIdx.x == 0 && threadIdx.x == 0 && read_displacement(disp) > 0.f) {
-    // particles moved since the binning (a predictor ran) but the walk keeps
-    // the cells' own reach: pairs may be missed
-    set_error(&hdr->err, SPH_ERR_MARGIN);
-  }
-  if constexpr (LPT == 1) {
-    if (i < n) {
-      PairAcc acc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0u};
-      TargetData T{false, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, false, 0.f};
-      uint32_t c64 = 0;
-      // with modified DBC the wall densities come from Eq. 38 (sph_mdbc): wall
-      // targets take no sums
-      if (!is_excluded(type[i]) && (kp.boundary == 0 || is_fluid(type[i]))) {
-        const float4 pa = pr[i], va = vp[i];
-        T.fluid = pa.w > 0.f;
-        T.rho = fabsf(pa.w);
-        T.irho = __builtin_amdgcn_rcpf(T.rho);
-        T.ik = kp.kvc_f * T.irho;
-        T.p = va.w;
-        T.vx = va.x;
-        T.vy = va.y;
-        T.vz = va.z;
-        T.flt = GEN && kp.floating && is_floating(type[i]);
-        const uint32_t k = key[i];
-        const int cx = (int)(k % (uint32_t)kp.ncx);
-        const uint32_t rest = k / (uint32_t)kp.ncx;
-        const int cy = (int)(rest % (uint32_t)kp.ncy);
-        const int cz = (int)(rest / (uint32_t)kp.ncy);
-        gather_walk<DIM, R, DIAG, EQM, GEN, PER>(kp, 0u, n, i, pa, T, cx, cy, cz, pr, vp, cstart,
-                                                pos64, acc, c64, cull2);
-        if (T.fluid) acc.cnt -= 1u;  // the self pair: counted, added nothing
-        const uint32_t c = DIAG ? c64 : acc.cnt;
-        write_target<DIM>(kp, n, i, T, acc, c, ace, arho, visc, nbr, fmag, vmax_out, nfl);
-        cnt_out = acc.cnt;
-        cnt_wall = T.fluid ? 0u : acc.cnt;
-      } else {
-        write_zero<DIM>(n, i, ace, arho, visc, nbr);
-      }
-    }
-  } else {
-    PairAcc acc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0u};
-    TargetData T{false, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, false, 0.f};
-    uint32_t c64 = 0;
-    const bool active =
-        i < n && !is_excluded(type[i]) && (kp.boundary == 0 || is_fluid(type[i]));
-    if (active) {
-      target_data<GEN>(kp, i, pr, vp, type, T);
-      int cx, cy, cz;
-      key_cell(kp, key[i], cx, cy, cz);
-      gather_walk<DIM, R, DIAG, EQM, GEN, PER, LPT>(kp, 0u, n, i, pr[i], T, cx, cy, cz, pr, vp,
-                                                    cstart, pos64, acc, c64, cull2, sub);
-    }
-    combine_lanes<LPT>(acc, c64);  // every lane: the sums of its target's lanes
-    if (i < n && sub == 0) {
-      if (active) {
-        if (T.fluid) acc.cnt -= 1u;  // the self pair: counted, added nothing
-        const uint32_t c = DIAG ? c64 : acc.cnt;
-        write_target<DIM>(kp, n, i, T, acc, c, ace, arho, visc, nbr, fmag, vmax_out, nfl);
-        cnt_out = acc.cnt;
-        cnt_wall = T.fluid ? 0u : acc.cnt;
-      } else {
-        write_zero<DIM>(n, i, ace, arho, visc, nbr);
-      }
-    }
-  }
-  write_block_red<kBlock / 64>(fmag, vmax_out, cnt_out, cnt_wall, nfl, red, hdr);
-}
 
 // ---------------------------------------------- precision-study arms --
 // Two reference forms of the interaction for the precision study of
@@ -273,24 +151,6 @@ __global__ __launch_bounds__(kBlock) void k_interact_arm(
   write_block_red<kBlock / 64>(fmag, vmax_out, cnt_out, cnt_wall, nfl, red, hdr);
 }
 
-// Lanes per target for a case of n particles.  One wavefront that walks its
-// targets' rows alone takes about 100 us in 3-D and 17 us in 2-D, whatever
-// the case's size: a chain of dependent loads (ranges, candidates,
-// velocities, row after row).  While wavefronts are too few to hide it,
-// dealing the rows to more lanes shortens the chain; once the GPU is full the
-// extra instructions cost (rows of different lengths in step, the sums over
-// lanes).  The lines lie where measured times cross (us per pass, 1 / 2 / 4 /
-// 8 / 16 lanes; 3-D dam breaks and 2-D dam breaks, one MI355X):
-//   3-D   13k: 104 / 60 / 36 / 23 / 19      25k: 102 / 59 / 36 / 28 / 28
-//         66k: 105 / 64 / 50 / 50 / 55     127k: 121 / 81 / 84 / 89 / 106
-//        223k: 164 / 124 / 144 / 158 / 189  441k: 220 / 234 / 292 / 321 / 387
-//   2-D   14k: 17 / 12 / 9.7 / 9.6 / 10     54k: 18 / 14 / 15 / 16 / 24
-//        185k: 25 / 27 / 33 / 41 / 69
-static int lanes_per_target(int dim, int64_t n) {
-  if (dim == 2) return n <= 32768 ? 4 : n <= 122880 ? 2 : 1;
-  return n <= 24576 ? 16 : n <= 65536 ? 8 : n <= 98304 ? 4 : n <= 327680 ? 2 : 1;
-}
-
 hipError_t launch_interact(const KParams& kp, int64_t n, const sph_state& s, const uint32_t* key,
                            const uint32_t* cell_start, float* ace, float* arho, float* visc,
                            uint32_t* nbr, uint32_t flags, void* ws, hipStream_t st) {
@@ -331,59 +191,9 @@ hipError_t launch_interact_on(const KParams& kp, int64_t n, const sph_state& s,
 #undef SPH_ARM
     return hipGetLastError();
   }
-  const bool diag = (flags & SPH_DIAG_COUNT_F64) != 0;
-  // reused cells: one more cell of reach (the kernels read the displacement)
-  const int reach = kp.cell_div + ((flags & SPH_INTERACT_REUSE_CELLS) ? 1 : 0);
-  const bool eqm = kp.mass_f == kp.mass_b;
-  const bool gen = kp.kernel != 0 || kp.viscosity != 0 || kp.ddt == 2 || kp.floating != 0;
-  const bool per = kp.periodic != 0;  // periodic cases run the general kernel with PER
-  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n);
-  // the diagnostic count and unequal masses come with one lane or four
-  if ((diag || !eqm) && lanes > 1) lanes = 4;
-#define SPH_LAUNCH(D, RR, G, PP, GG, PE, LP)                                                  \
-  hipLaunchKernelGGL((k_interact_gather<D, RR, G, PP, GG, PE, LP>),                           \
-                     dim3(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u),           \
-                     dim3(kBlock), 0, st, kp, n, pr, vp, key, cell_start, s.type, s.pos, ace, \
-                     arho, visc, nbr, red, hdr, w.disp)
-// the formulation: periodic cases run the general kernel with PER
-#define SPH_LAUNCH_F(D, RR, G, PP, LP)                  \
-  if (per) SPH_LAUNCH(D, RR, G, PP, true, true, LP);    \
-  else if (gen) SPH_LAUNCH(D, RR, G, PP, true, false, LP); \
-  else SPH_LAUNCH(D, RR, G, PP, false, false, LP)
-#define SPH_LAUNCH_1(D, RR, G, PP)                      \
-  if (lanes == 1) { SPH_LAUNCH_F(D, RR, G, PP, 1); }    \
-  else { SPH_LAUNCH_F(D, RR, G, PP, 4); }
-#define SPH_LAUNCH_2(RR)                                         \
-  if (lanes == 1) { SPH_LAUNCH_F(2, RR, false, true, 1); }       \
-  else if (lanes == 2) { SPH_LAUNCH_F(2, RR, false, true, 2); }  \
-  else { SPH_LAUNCH_F(2, RR, false, true, 4); }
-#define SPH_LAUNCH_3(RR)                                         \
-  if (lanes == 1) { SPH_LAUNCH_F(3, RR, false, true, 1); }       \
-  else if (lanes == 2) { SPH_LAUNCH_F(3, RR, false, true, 2); }  \
-  else if (lanes == 4) { SPH_LAUNCH_F(3, RR, false, true, 4); }  \
-  else if (lanes == 8) { SPH_LAUNCH_F(3, RR, false, true, 8); }  \
-  else { SPH_LAUNCH_F(3, RR, false, true, 16); }
-#define SPH_LAUNCH_R(D, RR)                                      \
-  if (diag && eqm) { SPH_LAUNCH_1(D, RR, true, true); }          \
-  else if (diag) { SPH_LAUNCH_1(D, RR, true, false); }           \
-  else if (!eqm) { SPH_LAUNCH_1(D, RR, false, false); }          \
-  else { SPH_LAUNCH_##D(RR); }
-  if (kp.dim == 2) {
-    if (reach == 1) { SPH_LAUNCH_R(2, 1); }
-    else if (reach == 2) { SPH_LAUNCH_R(2, 2); }
-    else { SPH_LAUNCH_R(2, 3); }
-  } else {
-    if (reach == 1) { SPH_LAUNCH_R(3, 1); }
-    else if (reach == 2) { SPH_LAUNCH_R(3, 2); }
-    else { SPH_LAUNCH_R(3, 3); }
-  }
-#undef SPH_LAUNCH_R
-#undef SPH_LAUNCH_3
-#undef SPH_LAUNCH_2
-#undef SPH_LAUNCH_1
-#undef SPH_LAUNCH_F
-#undef SPH_LAUNCH
-  return hipGetLastError();
+  return kp.dim == 2
+             ? launch_gather<2>(kp, n, s, key, cell_start, ace, arho, visc, nbr, flags, w, st)
+             : launch_gather<3>(kp, n, s, key, cell_start, ace, arho, visc, nbr, flags, w, st);
 }
 
 }  // namespace sph
