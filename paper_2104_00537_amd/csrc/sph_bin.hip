@@ -36,6 +36,7 @@ __global__ __launch_bounds__(kBlock) void k_count_cells(
   if (i == 0) {
     for (int k = 0; k < kDispSlots; ++k) disp[k] = 0u;
     hdr->bin_gen = hdr->bin_gen + 1u;
+    hdr->one_lane = 0u;
   }
   const uint32_t k = i < n ? cell_key_local(kp, pos, type, n, i) : 0u;
   const bool excluded = i < n && k == kp.ncell_total;

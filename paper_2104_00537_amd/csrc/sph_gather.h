@@ -53,6 +53,7 @@ __global__ __launch_bounds__(kBlock) void k_interact_gather(
   const int sub = (int)(t % LPT);
   float fmag = 0.f, vmax_out = 0.f;
   uint32_t cnt_out = 0, cnt_wall = 0, nfl = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) hdr->one_lane = LPT == 1 ? 1u : 0u;
   // cells reused after a view refresh (R above the cells' own stencil): cull
   // with the support widened by the largest displacement since the binning
   float cull2 = kp.support2_f * 1.0002f;
@@ -109,9 +110,10 @@ __global__ __launch_bounds__(kBlock) void k_interact_gather(
         i < n && !is_excluded(type[i]) && (kp.boundary == 0 || is_fluid(type[i]));
     if (active) {
       target_data<GEN>(kp, i, pr, vp, type, T);
+      const float4 pa = pr[i];
       int cx, cy, cz;
       key_cell(kp, key[i], cx, cy, cz);
-      gather_walk<DIM, R, DIAG, EQM, GEN, PER, LPT>(kp, 0u, n, i, pr[i], T, cx, cy, cz, pr, vp,
+      gather_walk<DIM, R, DIAG, EQM, GEN, PER, LPT>(kp, 0u, n, i, pa, T, cx, cy, cz, pr, vp,
                                                     cstart, pos64, acc, c64, cull2, sub);
     }
     combine_lanes<LPT>(acc, c64);  // every lane: the sums of its target's lanes

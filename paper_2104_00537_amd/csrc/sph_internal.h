@@ -75,6 +75,8 @@ struct WsHeader {
   uint32_t nwall;    // wall particles listed by the last sph_mdbc (its work list)
   uint32_t bin_gen;  // binnings so far (modulo 2^32): a neighbour list records
                      // the binning it was built on
+  uint32_t one_lane;    // the last interaction since the binning took one lane per
+                        // target: a shifting on its view does too
   uint32_t list_walks;  // list passes that walked the cells instead (every
                         // target: the displacement exceeded the list's skin)
   uint32_t skin_hint;   // bits of the skin the last list pass on reused

@@ -234,6 +234,16 @@ __device__ __forceinline__ const T& at_byte(const T* __restrict__ base, uint32_t
   return *(reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + o) + U);
 }
 
+// The positions of NU consecutive candidates from byte offset o of the view.
+template <int NU>
+__device__ __forceinline__ void load_group(const float4* __restrict__ pr, uint32_t o,
+                                           float4 (&pb)[NU]) {
+  pb[0] = at_byte<0>(pr, o);
+  if (NU > 1) pb[1 % NU] = at_byte<1>(pr, o);
+  if (NU > 2) pb[2 % NU] = at_byte<2>(pr, o);
+  if (NU > 3) pb[3 % NU] = at_byte<3>(pr, o);
+}
+
 // One group of NU (4, 2 or 1) consecutive candidates j..j+NU-1 of a row for
 // one target lane, all before the row's end j1 (o = 16 j and o1 = 16 j1 are
 // byte offsets into the views: 32 bits, which the calls' limit of n < 2^28
@@ -255,10 +265,7 @@ __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64
                                              const double* __restrict__ pos64, PairAcc& acc,
                                              uint32_t& c64) {
   float4 pb[NU];
-  pb[0] = at_byte<0>(pr, o);
-  if (NU > 1) pb[1 % NU] = at_byte<1>(pr, o);
-  if (NU > 2) pb[2 % NU] = at_byte<2>(pr, o);
-  if (NU > 3) pb[3 % NU] = at_byte<3>(pr, o);
+  load_group<NU>(pr, o, pb);
   bool hit[NU];
   float dxs[NU], dys[NU], dzs[NU], r2s[NU];
 #pragma unroll
@@ -303,8 +310,7 @@ __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64
 // only |x_ab| < sqrt(4h^2 - e_y^2 - e_z^2) can hold a neighbour (rows with a
 // negative radicand are skipped).  The cut uses a support enlarged by 1e-4
 // relative, far above the FP32 error of the offsets, so that no pair within
-// 2h is ever cut.  Each range runs as whole groups of 4, then a group of 2
-// and a group of 1 for its last candidates.
+// 2h is ever cut.
 //
 // Periodic components (PER kernels only, Section 2.7): a row index along
 // y or z past either end wraps to the other end (the row's shift (ys, zs)
@@ -326,30 +332,21 @@ __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64
 // fixed-point period is at least 4 cells away either way, beyond 2h, so it
 // is never a neighbour.
 //
-// The target is not excluded from its own candidates: its self pair adds
-// exactly zero to every sum (v_aa = 0, r_aa = 0 and rho_a - rho_a = 0) and
-// the caller takes it off the count (fluid targets meet themselves; wall
-// targets skip wall candidates).  DIAG also counts neighbours with an FP64
-// test on the FP64 positions (c64, self excluded).
-//
-// LPT > 1: the rows of the stencil are dealt to LPT lanes (by position in
-// the stencil, lane `sub` taking every LPT-th), which shortens each lane's
+// LPT > 1: the rows of the stencil are dealt to `stride` lanes, LPT or fewer
+// (by position in the stencil, lane `sub` taking every stride-th), which shortens each lane's
 // chain of dependent loads for cases too small to fill the GPU; the caller
-// sums the lanes' partial results (combine_lanes).
-template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT = 1>
-__device__ __forceinline__ void gather_walk(const KParams& kp, uint32_t cbase, int64_t n,
-                                            int64_t i, const float4& pa, const TargetData& T,
-                                            int cx, int cy, int cz,
-                                            const float4* __restrict__ pr,
-                                            const float4* __restrict__ vp,
-                                            const uint32_t* __restrict__ cstart,
-                                            const double* __restrict__ pos64, PairAcc& acc,
-                                            uint32_t& c64, float cull2, int sub = 0) {
+// sums the lanes' partial results.
+//
+// walk(o, o1, xv, ys, zs) is called for every candidate range: byte offsets o to
+// o1 in the views, the target's x bits xv and its offsets (ys, zs) in the
+// range's frame.
+template <int DIM, int R, bool PER, int LPT, typename Walk>
+__device__ __forceinline__ void walk_rows(const KParams& kp, uint32_t cbase, const float4& pa,
+                                          int cx, int cy, int cz,
+                                          const uint32_t* __restrict__ cstart, float cull2,
+                                          int sub, int stride, Walk&& walk) {
   static_assert(R <= 3, "the x period (8 cells) must exceed twice the stencil reach");
   static_assert(kFrameCells == 8, "x offsets use 2^29 units per cell");
-  double pa64[3] = {0.0, 0.0, 0.0};
-  if (DIAG)
-    for (int d = 0; d < DIM; ++d) pa64[d] = pos64[d * n + i];
   const float cs = kp.cs_f;
   const uint32_t xa = __float_as_uint(pa.x);
   // the target's offset inside its own key cell along x (key cells of
@@ -392,49 +389,71 @@ __device__ __forceinline__ void gather_walk(const KParams& kp, uint32_t cbase, i
         cbase + (uint32_t)kp.ncx * ((uint32_t)y + (uint32_t)kp.ncy * (uint32_t)z);
     const float ys = row_shift(pa.y, dy, cs), zs = row_shift(pa.z, dz, cs);
     // the candidates of key cells [c0, c1] of the row, with target x bits xv
-    auto walk = [&](int c0, int c1, uint32_t xv) {
-      // byte offsets of the range in the views
-      uint32_t o = at32(cstart, row + c0) * 16u;
-      const uint32_t o1 = at32(cstart, row + c1 + 1) * 16u;
-      for (; o + 64u <= o1; o += 64u)
-        gather_group<DIM, DIAG, EQM, GEN, PER>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64, pos64,
-                                               acc, c64);
-      // the last 0-3 candidates as a group of 2 and a group of 1 (a masked
-      // group of 4 would test up to 3 slots past the range)
-      if (o + 32u <= o1) {
-        gather_group<DIM, DIAG, EQM, GEN, PER, 2>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64,
-                                                  pos64, acc, c64);
-        o += 32u;
-      }
-      if (o < o1)
-        gather_group<DIM, DIAG, EQM, GEN, PER, 1>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64,
-                                                  pos64, acc, c64);
+    auto range = [&](int c0, int c1, uint32_t xv) {
+      walk(at32(cstart, row + c0) * 16u, at32(cstart, row + c1 + 1) * 16u, xv, ys, zs);
     };
     if (perx) {
       if (x0 < 0) {  // cells at the far end, one period below
-        walk(kp.ncx + x0, kp.ncx - 1, xa + kp.lu);
+        range(kp.ncx + x0, kp.ncx - 1, xa + kp.lu);
         x0 = 0;
       }
       if (x1 >= kp.ncx) {  // cells at the near end, one period above
-        walk(0, x1 - kp.ncx, xa - kp.lu);
+        range(0, x1 - kp.ncx, xa - kp.lu);
         x1 = kp.ncx - 1;
       }
     }
-    walk(x0, x1, xa);
+    range(x0, x1, xa);
   };
   if constexpr (LPT == 1) {
     for (int dz = zlo; dz <= zhi; ++dz)
       for (int dy = -R; dy <= R; ++dy) visit(dz, dy);
   } else {
-    // the LPT lanes of a target walk different rows at the same time: in
-    // round q, lane `sub` takes row q LPT + sub of the stencil
+    // the lanes of a target walk different rows at the same time: in round q,
+    // lane `sub` takes row q stride + sub of the stencil
     constexpr int kRowsY = 2 * R + 1;
     constexpr int kRows = kRowsY * (DIM == 3 ? 2 * R + 1 : 1);
-    for (int q = 0; q < (kRows + LPT - 1) / LPT; ++q) {
-      const int r = q * LPT + sub;
+    for (int q = 0; q < (kRows + stride - 1) / stride; ++q) {
+      const int r = q * stride + sub;
       if (r < kRows) visit(zlo + r / kRowsY, r % kRowsY - R);
     }
   }
+}
+
+// The candidate walk of one target lane (walk_rows) with the pair terms: each
+// range as whole groups of 4, then a group of 2 and a group of 1 for its last
+// candidates (a masked group of 4 would test up to 3 slots past the range).
+//
+// The target is not excluded from its own candidates: its self pair adds
+// exactly zero to every sum (v_aa = 0, r_aa = 0 and rho_a - rho_a = 0) and
+// the caller takes it off the count (fluid targets meet themselves; wall
+// targets skip wall candidates).  DIAG also counts neighbours with an FP64
+// test on the FP64 positions (c64, self excluded).
+template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT = 1>
+__device__ __forceinline__ void gather_walk(const KParams& kp, uint32_t cbase, int64_t n,
+                                            int64_t i, const float4& pa, const TargetData& T,
+                                            int cx, int cy, int cz,
+                                            const float4* __restrict__ pr,
+                                            const float4* __restrict__ vp,
+                                            const uint32_t* __restrict__ cstart,
+                                            const double* __restrict__ pos64, PairAcc& acc,
+                                            uint32_t& c64, float cull2, int sub = 0) {
+  double pa64[3] = {0.0, 0.0, 0.0};
+  if (DIAG)
+    for (int d = 0; d < DIM; ++d) pa64[d] = pos64[d * n + i];
+  auto walk = [&](uint32_t o, uint32_t o1, uint32_t xv, float ys, float zs) {
+    for (; o + 64u <= o1; o += 64u)
+      gather_group<DIM, DIAG, EQM, GEN, PER>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64, pos64, acc,
+                                             c64);
+    if (o + 32u <= o1) {
+      gather_group<DIM, DIAG, EQM, GEN, PER, 2>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64, pos64,
+                                                acc, c64);
+      o += 32u;
+    }
+    if (o < o1)
+      gather_group<DIM, DIAG, EQM, GEN, PER, 1>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64, pos64,
+                                                acc, c64);
+  };
+  walk_rows<DIM, R, PER, LPT>(kp, cbase, pa, cx, cy, cz, cstart, cull2, sub, LPT, walk);
 }
 
 // Sums the walks of the LPT lanes of each target (adjacent lanes, LPT a

@@ -4,121 +4,128 @@
 // Two gathers over the interaction view of the state n+1/2: the
 // concentration C of every particle, then, for fluid particles, its
 // gradient and the shift, added to the corrected FP64 positions.  One lane
-// per particle in sorted order, blocks placed per XCD as in the
-// interaction; sums per lane, no atomics.
+// per particle in sorted order (a few where the case is too small to fill the
+// GPU), blocks placed per XCD as in the interaction; sums per lane, no
+// atomics.  Bound by the candidates' 16 bytes through the L1 data path (0.86
+// busy at 958k particles) and, for small cases, by the latency of the loads.
 #include "sph_kernels.h"
+#include "sph_pair.h"
 #include "sph_slots.h"
 
 namespace sph {
 
-// Visits every candidate b within 2h of a target (view position pa, key
-// cell (cx, cy, cz), cell keys offset by cbase): the rows of the neighbour
-// cells, each cut to the key cells the support sphere reaches, as in the
-// interaction's walk (periodic components wrapped the same way when PER), in
-// groups of 4 candidates.  Calls f(j, dx, dy, dz, r2, pb) with
-// r_ab = (dx, dy, dz) and |r_ab|^2 < 4h^2.
-template <int DIM, int R, bool PER, typename F>
-__device__ inline void visit_neighbours(const KParams& kp, uint32_t cbase, const float4& pa,
-                                        int cx, int cy, int cz, const float4* __restrict__ pr,
-                                        const uint32_t* __restrict__ cstart, float cull2,
-                                        F&& f) {
-  const float cs = kp.cs_f;
-  const uint32_t xa = __float_as_uint(pa.x);
-  const int fcells = kFrameCells << kp.lg_xsub;
-  const float fx =
-      (float)(int32_t)(xa - ((uint32_t)(cx % fcells) << (29 - kp.lg_xsub))) * kp.unit_x_f;
-  const int reach = R * kp.x_sub;
-  const bool perx = PER && (kp.periodic & 1);
-  const bool pery = PER && (kp.periodic & 2);
-  const bool perz = PER && DIM == 3 && (kp.periodic & 4);
-  const int xlo = cx - reach < 0 && !perx ? 0 : cx - reach;
-  const int xhi = cx + reach >= kp.ncx && !perx ? kp.ncx - 1 : cx + reach;
-  const int zlo = DIM == 3 ? -R : 0, zhi = DIM == 3 ? R : 0;
-  for (int dz = zlo; dz <= zhi; ++dz) {
-    int z = cz + dz;
-    if (z < 0 || z >= kp.ncz) {
-      if (!perz) continue;
-      z += z < 0 ? kp.ncz : -kp.ncz;
-    }
-    const float ez0 = (float)dz * cs - pa.z;
-    const float ez = dz > 0 ? ez0 : (dz < 0 ? -(ez0 + cs) : 0.f);
-    for (int dy = -R; dy <= R; ++dy) {
-      int y = cy + dy;
-      if (y < 0 || y >= kp.ncy) {
-        if (!pery) continue;
-        y += y < 0 ? kp.ncy : -kp.ncy;
-      }
-      const float ey0 = (float)dy * cs - pa.y;
-      const float ey = dy > 0 ? ey0 : (dy < 0 ? -(ey0 + cs) : 0.f);
-      const float w2 = cull2 - ey * ey - ez * ez;
-      if (!(w2 > 0.f)) continue;
-      const float w = __builtin_amdgcn_sqrtf(w2);
-      int x0 = cx + (int)floorf((fx - w) * kp.inv_csx_f);
-      int x1 = cx + (int)floorf((fx + w) * kp.inv_csx_f);
-      x0 = x0 < xlo ? xlo : x0;
-      x1 = x1 > xhi ? xhi : x1;
-      const uint32_t row =
-          cbase + (uint32_t)kp.ncx * ((uint32_t)y + (uint32_t)kp.ncy * (uint32_t)z);
-      const float ys = pa.y - (float)dy * cs, zs = pa.z - (float)dz * cs;
-      // candidates 4 at a time, all loads in flight (the view is padded by
-      // kViewPad entries, so a group may read past the last particle;
-      // those candidates are masked)
-      auto range = [&](int c0, int c1, uint32_t xv) {
-        const uint32_t j1 = cstart[row + c1 + 1];
-        for (uint32_t j = cstart[row + c0]; j < j1; j += 4) {
-          float4 pb[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) pb[u] = pr[j + u];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float dx = (float)(int32_t)(xv - __float_as_uint(pb[u].x)) * kp.unit_x_f;
-            const float ddy = ys - pb[u].y;
-            const float ddz = DIM == 3 ? zs - pb[u].z : 0.f;
-            // explicit fma chains: a zero component (2-D cases, and 2-D
-            // slots of a batch in the packed (x, 0, z) layout) adds exactly
-            // nothing, so both layouts round alike
-            const float r2 = fmaf(ddz, ddz, fmaf(ddy, ddy, dx * dx));
-            if (j + u < j1 && r2 < kp.support2_f) f(j + u, dx, ddy, ddz, r2, pb[u]);
-          }
-        }
-      };
-      if (perx) {
-        if (x0 < 0) {
-          range(kp.ncx + x0, kp.ncx - 1, xa + kp.lu);
-          x0 = 0;
-        }
-        if (x1 >= kp.ncx) {
-          range(0, x1 - kp.ncx, xa - kp.lu);
-          x1 = kp.ncx - 1;
-        }
-      }
-      range(x0, x1, xa);
-    }
-  }
-}
-
-// W(r) of the case's kernel: Wendland C2 (Eq. 11) alpha_D (1 - q/2)^4 (2q + 1)
+// W(r) / w_alpha of the case's kernel: Wendland C2 (Eq. 11) (1 - q/2)^4 (2q + 1)
 // or cubic spline (Eq. 10).
 __device__ inline float kernel_w_f(const KParams& kp, float r2) {
   const float q = __builtin_amdgcn_sqrtf(r2) * kp.inv_h_f;
   if (kp.kernel == 0) {
     const float w = fmaf(-0.5f, q, 1.f), ww = w * w;
-    return kp.w_alpha_f * ww * ww * fmaf(2.f, q, 1.f);
+    return ww * ww * fmaf(2.f, q, 1.f);
   }
-  if (q <= 1.f) return kp.w_alpha_f * fmaf(q * q, fmaf(0.75f, q, -1.5f), 1.f);
+  if (q <= 1.f) return fmaf(q * q, fmaf(0.75f, q, -1.5f), 1.f);
   const float u = 2.f - q;
-  return kp.w_alpha_f * 0.25f * u * u * u;
+  return 0.25f * u * u * u;
 }
 
-// F_ab with grad_a W_ab = F_ab r_ab (as in the interaction's pair terms).
-__device__ inline float kernel_f_f(const KParams& kp, float kfab, float r2) {
+// F_ab / kfab with grad_a W_ab = F_ab r_ab (as in the interaction's pair terms).
+__device__ inline float kernel_f_f(const KParams& kp, float r2) {
   const float s = __builtin_amdgcn_sqrtf(r2);
   if (kp.kernel == 0) {
     const float w = fmaf(s, kp.mhalf_inv_h_f, 1.f);
-    return kfab * w * w * w;
+    return w * w * w;
   }
   const float q = s * kp.inv_h_f, u = 2.f - q;
-  return kfab * (q <= 1.f ? fmaf(2.25f, q, -3.f) : -0.75f * u * u * __builtin_amdgcn_rcpf(q));
+  return q <= 1.f ? fmaf(2.25f, q, -3.f) : -0.75f * u * u * __builtin_amdgcn_rcpf(q);
+}
+
+// The sums of a target over its neighbours: C_a / (m_f w_alpha) (GRAD false), or
+// grad C_a / (m_f kfab).
+template <int DIM, bool GRAD>
+struct ShiftAcc {
+  float s[GRAD ? DIM : 1];
+};
+
+// One group of 4 consecutive candidates from byte offset o of the view (see
+// gather_group): positions loaded together and tested, then for the gradient
+// the concentrations of the hits, then their terms.  LAST: only the candidates
+// before byte offset o1 count (the view is padded by kViewPad entries).
+template <int DIM, bool GRAD, bool LAST>
+__device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, float ys, float zs,
+                                            uint32_t o, uint32_t o1, const float4* __restrict__ pr,
+                                            const float* __restrict__ conc, float ca,
+                                            ShiftAcc<DIM, GRAD>& acc) {
+  constexpr int NU = 4;
+  float4 pb[NU];
+  load_group<NU>(pr, o, pb);
+  bool hit[NU];
+  float dxs[NU], dys[NU], dzs[NU], r2s[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    r2s[u] = pair_geom<DIM>(kp, xa, ys, zs, pb[u], dxs[u], dys[u], dzs[u]);
+    hit[u] = r2s[u] < kp.support2_f && (!LAST || o + 16u * u < o1);
+    // (the density is loaded with the position: left alone, the compiler loads
+    // it by itself once the test has passed)
+    asm volatile("" ::"v"(pb[u].w));
+  }
+  float cb[NU];
+  if (GRAD) {
+    const uint32_t oc = o >> 2;
+    if (hit[0]) cb[0] = at_byte<0>(conc, oc);
+    if (hit[1]) cb[1] = at_byte<1>(conc, oc);
+    if (hit[2]) cb[2] = at_byte<2>(conc, oc);
+    if (hit[3]) cb[3] = at_byte<3>(conc, oc);
+  }
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    if (!hit[u]) continue;
+    const float vb =  // V_b / m_f
+        (pb[u].w > 0.f ? 1.f : kp.mass_ratio_f) * __builtin_amdgcn_rcpf(fabsf(pb[u].w));
+    if (GRAD) {
+      const float w = vb * (cb[u] - ca) * kernel_f_f(kp, r2s[u]);
+      acc.s[0] = fmaf(w, dxs[u], acc.s[0]);
+      acc.s[1 % (GRAD ? DIM : 1)] = fmaf(w, dys[u], acc.s[1 % (GRAD ? DIM : 1)]);
+      if (DIM == 3) acc.s[2 % (GRAD ? DIM : 1)] = fmaf(w, dzs[u], acc.s[2 % (GRAD ? DIM : 1)]);
+    } else {
+      acc.s[0] = fmaf(vb, kernel_w_f(kp, r2s[u]), acc.s[0]);
+    }
+  }
+}
+
+// The sums of one target (view position pa, key cell (cx, cy, cz), cell keys
+// offset by cbase) over the rows of lane `sub` of its LPT (walk_rows): each
+// range as whole groups of 4 and a masked one.
+template <int DIM, int R, bool PER, bool GRAD, int LPT>
+__device__ __forceinline__ ShiftAcc<DIM, GRAD> shift_walk(const KParams& kp, uint32_t cbase,
+                                               const float4& pa, int cx, int cy, int cz,
+                                               const float4* __restrict__ pr,
+                                               const uint32_t* __restrict__ cstart, float cull2,
+                                               const float* __restrict__ conc, float ca,
+                                               int sub, int stride) {
+  ShiftAcc<DIM, GRAD> acc{};
+  auto walk = [&](uint32_t o, uint32_t o1, uint32_t xv, float ys, float zs) {
+    for (; o + 64u <= o1; o += 64u)
+      shift_group<DIM, GRAD, false>(kp, xv, ys, zs, o, o1, pr, conc, ca, acc);
+    if (o < o1) shift_group<DIM, GRAD, true>(kp, xv, ys, zs, o, o1, pr, conc, ca, acc);
+  };
+  walk_rows<DIM, R, PER, LPT>(kp, cbase, pa, cx, cy, cz, cstart, cull2, sub, stride, walk);
+  return acc;
+}
+
+// The sum of v over the `lanes` adjacent lanes of a target (uniform), in every lane.
+__device__ inline float lanes_sum(float v, int lanes) {
+  for (int off = 1; off < lanes; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// The target, the lane's place among the target's lanes and their number, LPT or
+// one: after an interaction with one lane per target, shifting takes one too
+// (thread t target t, the sums in the order of the one-lane kernel).
+template <int LPT>
+__device__ inline int64_t shift_lane(const WsHeader* __restrict__ hdr, int& sub, int& lanes) {
+  const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+  lanes = LPT > 1 && hdr->one_lane == 0u ? LPT : 1;
+  sub = lanes == 1 ? 0 : (int)(t % LPT);
+  return lanes == 1 ? t : t / LPT;
 }
 
 __device__ inline void target_cell(const KParams& kp, uint32_t k, int& cx, int& cy, int& cz) {
@@ -151,54 +158,59 @@ __device__ inline float shift_cull2(const KParams& kp, const uint32_t* __restric
   return rc * rc;
 }
 
-// C_a of one non-excluded target (local key lk, cell keys offset by cbase).
-template <int DIM, int R, bool PER>
-__device__ inline float conc_one(const KParams& kp, uint32_t cbase, uint32_t lk, const float4& pa,
+// C_a of one target (local key lk, cell keys offset by cbase) in every lane of
+// its LPT; lanes without a target (`live` false) take part in the sums over lanes.
+template <int DIM, int R, bool PER, int LPT>
+__device__ inline float conc_one(const KParams& kp, bool live, uint32_t cbase, int64_t i,
                                  const float4* __restrict__ pr,
-                                 const uint32_t* __restrict__ cstart, float cull2) {
-  const float mf = (float)kp.mass_f, mw = (float)kp.mass_b;
-  int cx, cy, cz;
-  target_cell(kp, lk, cx, cy, cz);
-  float c = 0.f;
-  visit_neighbours<DIM, R, PER>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
-                                [&](uint32_t, float, float, float, float r2, const float4& pb) {
-                                  const float vb = (pb.w > 0.f ? mf : mw) *
-                                                   __builtin_amdgcn_rcpf(fabsf(pb.w));
-                                  c = fmaf(vb, kernel_w_f(kp, r2), c);
-                                });
-  return c;
+                                 const uint32_t* __restrict__ key,
+                                 const uint32_t* __restrict__ cstart, float cull2, int sub,
+                                 int lanes) {
+  ShiftAcc<DIM, false> acc{};
+  if (live) {
+    const float4 pa = pr[i];
+    int cx, cy, cz;
+    target_cell(kp, key[i] - cbase, cx, cy, cz);
+    acc = shift_walk<DIM, R, PER, false, LPT>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
+                                              nullptr, 0.f, sub, lanes);
+  }
+  return ((float)kp.mass_f * kp.w_alpha_f) * lanes_sum(acc.s[0], lanes);
 }
 
 // grad C_a = sum_b V_b (C_b - C_a) F_ab r_ab and dr_a = -A_s h |v_a| dt grad C_a
 // (Eq. 40-41, 53) for one fluid target i, with the tangential projection
 // below the surface threshold (Eq. 54, a_n = 0); dr_a is added to the
-// positions (and written to `shift` when given).
-template <int DIM, int R, bool PER>
-__device__ inline void shift_one(const KParams& kp, uint32_t cbase, uint32_t lk, int64_t n,
+// positions (and written to `shift` when given) by lane 0 of the target's LPT.
+template <int DIM, int R, bool PER, int LPT>
+__device__ inline void shift_one(const KParams& kp, bool live, uint32_t cbase, int64_t n,
                                  int64_t i, const float4* __restrict__ pr,
                                  const float4* __restrict__ vp,
+                                 const uint32_t* __restrict__ key,
                                  const uint32_t* __restrict__ cstart,
-                                 const float* __restrict__ conc, double dt, float cull2,
-                                 double* __restrict__ pos, float* __restrict__ shift) {
-  const float mf = (float)kp.mass_f, mw = (float)kp.mass_b, kfab = (float)kp.kfab;
-  const float4 pa = pr[i], va = vp[i];
-  const float ca = conc[i];
-  int cx, cy, cz;
-  target_cell(kp, lk, cx, cy, cz);
-  float g0 = 0.f, g1 = 0.f, g2 = 0.f;
-  visit_neighbours<DIM, R, PER>(
-      kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
-      [&](uint32_t j, float dx, float dy, float dz, float r2, const float4& pb) {
-        const float vb = (pb.w > 0.f ? mf : mw) * __builtin_amdgcn_rcpf(fabsf(pb.w));
-        const float w = vb * (conc[j] - ca) * kernel_f_f(kp, kfab, r2);
-        g0 = fmaf(w, dx, g0);
-        g1 = fmaf(w, dy, g1);
-        g2 = fmaf(w, dz, g2);
-      });
-  // sums over components as explicit fma chains (see visit_neighbours)
+                                 const float* __restrict__ conc, const double* __restrict__ dtp,
+                                 float cull2, double* __restrict__ pos, float* __restrict__ shift,
+                                 int sub, int lanes) {
+  ShiftAcc<DIM, true> acc{};
+  float ca = 0.f;
+  if (live) {
+    ca = conc[i];
+    const float4 pa = pr[i];
+    int cx, cy, cz;
+    target_cell(kp, key[i] - cbase, cx, cy, cz);
+    acc = shift_walk<DIM, R, PER, true, LPT>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
+                                             conc, ca, sub, lanes);
+  }
+  const float kfab = kp.kfab_mf_f;
+  const float g0 = kfab * lanes_sum(acc.s[0], lanes), g1 = kfab * lanes_sum(acc.s[1], lanes),
+              g2 = DIM == 3 ? kfab * lanes_sum(acc.s[DIM - 1], lanes) : 0.f;
+  if (!live || sub != 0) return;
+  // sums over components as explicit fma chains: a zero component (2-D cases,
+  // and 2-D slots of a batch in the packed (x, 0, z) layout) adds exactly
+  // nothing, so both layouts round alike
+  const float4 va = vp[i];
   const float speed =
       __builtin_amdgcn_sqrtf(fmaf(va.z, va.z, fmaf(va.y, va.y, va.x * va.x)));
-  const float ds = kp.shift_k_f * speed * (float)dt;
+  const float ds = kp.shift_k_f * speed * (float)*dtp;
   float d[3] = {-ds * g0, -ds * g1, DIM == 3 ? -ds * g2 : 0.f};
   if (kp.shift_fs_f > 0.f && ca < kp.shift_fs_f) {
     const float gg = fmaf(g2, g2, fmaf(g1, g1, g0 * g0));
@@ -215,7 +227,7 @@ __device__ inline void shift_one(const KParams& kp, uint32_t cbase, uint32_t lk,
   }
 }
 
-template <int DIM, int R, bool PER>
+template <int DIM, int R, bool PER, int LPT>
 __global__ __launch_bounds__(kBlock) void k_shift_conc(KParams kp, int64_t n,
                                                        const float4* __restrict__ pr,
                                                        const uint32_t* __restrict__ key,
@@ -223,32 +235,31 @@ __global__ __launch_bounds__(kBlock) void k_shift_conc(KParams kp, int64_t n,
                                                        const uint8_t* __restrict__ type,
                                                        float* __restrict__ conc,
                                                        const uint32_t* __restrict__ disp,
-                                                       uint32_t* __restrict__ err) {
-  const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-  const float cull2 = shift_cull2<R>(kp, disp, err);
-  if (i >= n) return;
-  conc[i] = is_excluded(type[i])
-                ? 0.f
-                : conc_one<DIM, R, PER>(kp, 0u, key[i], pr[i], pr, cstart, cull2);
+                                                       WsHeader* __restrict__ hdr) {
+  int sub, lanes;
+  const int64_t i = shift_lane<LPT>(hdr, sub, lanes);
+  const float cull2 = shift_cull2<R>(kp, disp, &hdr->err);
+  const bool live = i < n && !is_excluded(type[i]);
+  const float c = conc_one<DIM, R, PER, LPT>(kp, live, 0u, i, pr, key, cstart, cull2, sub, lanes);
+  if (i < n && sub == 0) conc[i] = live ? c : 0.f;
 }
 
-template <int DIM, int R, bool PER>
+template <int DIM, int R, bool PER, int LPT>
 __global__ __launch_bounds__(kBlock) void k_shift_apply(
     KParams kp, int64_t n, const float4* __restrict__ pr, const float4* __restrict__ vp,
     const uint32_t* __restrict__ key, const uint32_t* __restrict__ cstart,
     const uint8_t* __restrict__ type, const float* __restrict__ conc,
     const double* __restrict__ dtp, double* __restrict__ pos, float* __restrict__ shift,
-    const uint32_t* __restrict__ disp, uint32_t* __restrict__ err) {
-  const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-  const float cull2 = shift_cull2<R>(kp, disp, err);
-  if (i >= n) return;
-  const uint8_t t = type[i];
-  if (!is_fluid(t) || is_excluded(t)) {
-    if (shift)
-      for (int d = 0; d < DIM; ++d) shift[d * n + i] = 0.f;
-    return;
-  }
-  shift_one<DIM, R, PER>(kp, 0u, key[i], n, i, pr, vp, cstart, conc, *dtp, cull2, pos, shift);
+    const uint32_t* __restrict__ disp, WsHeader* __restrict__ hdr) {
+  int sub, lanes;
+  const int64_t i = shift_lane<LPT>(hdr, sub, lanes);
+  const float cull2 = shift_cull2<R>(kp, disp, &hdr->err);
+  const uint8_t ty = i < n ? type[i] : (uint8_t)0;
+  const bool live = i < n && is_fluid(ty) && !is_excluded(ty);
+  if (i < n && !live && shift && sub == 0)
+    for (int d = 0; d < DIM; ++d) shift[d * n + i] = 0.f;
+  shift_one<DIM, R, PER, LPT>(kp, live, 0u, n, i, pr, vp, key, cstart, conc, dtp, cull2, pos,
+                              shift, sub, lanes);
 }
 
 // ------------------------------------------------------------- batches --
@@ -310,17 +321,28 @@ __global__ __launch_bounds__(kBlock) void k_batch_shift(
     if (!mine) continue;
     const uint8_t t = type[i];
     if (!APPLY) {
-      conc[i] = is_excluded(t)
-                    ? 0.f
-                    : conc_one<3, R, PER>(kp, cbase, key[i] - cbase, pr[i], pr, cstart, cull2);
-    } else if (!is_fluid(t) || is_excluded(t)) {
-      if (shift)
-        for (int d = 0; d < 3; ++d) shift[d * n + i] = 0.f;
+      const bool live = !is_excluded(t);
+      const float c = conc_one<3, R, PER, 1>(kp, live, cbase, i, pr, key, cstart, cull2, 0, 1);
+      conc[i] = live ? c : 0.f;
     } else {
-      shift_one<3, R, PER>(kp, cbase, key[i] - cbase, n, i, pr, vp, cstart, conc, dt[rs], cull2,
-                           pos, shift);
+      const bool live = is_fluid(t) && !is_excluded(t);
+      if (!live && shift)
+        for (int d = 0; d < 3; ++d) shift[d * n + i] = 0.f;
+      shift_one<3, R, PER, 1>(kp, live, cbase, n, i, pr, vp, key, cstart, conc, &dt[rs], cull2,
+                              pos, shift, 0, 1);
     }
   }
+}
+
+// Lanes per target for a case of n particles, as for the interaction
+// (lanes_per_target), of fewer kinds.  Measured, both kernels together, us with
+// 1 / 4 / 16 lanes (dam breaks on reused cells):
+//   3-D    6k: 168 / 70 / 34    25k: 174 / 71 / 48    38k: 173 / 74 / 65
+//         66k: 180 / 87 / 97   127k: 188 / 144 / 173  168k: 192 / 189 / 234
+//   2-D    4k: 27 / 16          54k: 29 / 23           84k: 30 / 31
+static int shift_lanes(int dim, int64_t n) {
+  if (dim == 2) return n <= 65536 ? 4 : 1;
+  return n <= 49152 ? 16 : n <= 163840 ? 4 : 1;
 }
 
 hipError_t launch_shifting(const KParams& kp, int64_t n, const sph_state& s, const uint32_t* key,
@@ -331,31 +353,38 @@ hipError_t launch_shifting(const KParams& kp, int64_t n, const sph_state& s, con
   const float4* vp = ws_ptr<float4>(ws, L.view_vp);
   float* c = conc ? conc : ws_ptr<float>(ws, L.keyA);
   const uint32_t* disp = ws_ptr<uint32_t>(ws, L.disp);
-  uint32_t* err = ws_ptr<uint32_t>(ws, L.err);
-  const unsigned grid = (unsigned)L.nblk_interact;
+  WsHeader* hdr = ws_ptr<WsHeader>(ws, L.err);
   const bool per = kp.periodic != 0;
+  const int lanes = shift_lanes(kp.dim, n);
   // reused cells: one more cell of reach, cut widened by the displacement
   const int reach = kp.cell_div + (reuse ? 1 : 0);
-#define SPH_SHIFT(D, RR, PE)                                                                  \
+#define SPH_SHIFT(D, RR, PE, LP)                                                              \
   do {                                                                                        \
-    hipLaunchKernelGGL((k_shift_conc<D, RR, PE>), dim3(grid), dim3(kBlock), 0, st, kp, n, pr, \
-                       key, cell_start, s.type, c, disp, err);                                \
-    hipLaunchKernelGGL((k_shift_apply<D, RR, PE>), dim3(grid), dim3(kBlock), 0, st, kp, n,    \
-                       pr, vp, key, cell_start, s.type, c, dt, s.pos, shift, disp, err);      \
+    const dim3 grid(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u);                 \
+    hipLaunchKernelGGL((k_shift_conc<D, RR, PE, LP>), grid, dim3(kBlock), 0, st, kp, n, pr,   \
+                       key, cell_start, s.type, c, disp, hdr);                                \
+    hipLaunchKernelGGL((k_shift_apply<D, RR, PE, LP>), grid, dim3(kBlock), 0, st, kp, n,      \
+                       pr, vp, key, cell_start, s.type, c, dt, s.pos, shift, disp, hdr);      \
   } while (0)
-#define SPH_SHIFT_P(D, RR) \
-  if (per) SPH_SHIFT(D, RR, true); else SPH_SHIFT(D, RR, false)
-#define SPH_SHIFT_R(D)                      \
-  if (reach == 1) SPH_SHIFT_P(D, 1);        \
-  else if (reach == 2) SPH_SHIFT_P(D, 2);   \
-  else SPH_SHIFT_P(D, 3)
+#define SPH_SHIFT_L2(RR, PE)                 \
+  if (lanes == 4) SPH_SHIFT(2, RR, PE, 4);   \
+  else SPH_SHIFT(2, RR, PE, 1)
+#define SPH_SHIFT_L3(RR, PE)                     \
+  if (lanes == 16) SPH_SHIFT(3, RR, PE, 16);     \
+  else if (lanes == 4) SPH_SHIFT(3, RR, PE, 4);  \
+  else SPH_SHIFT(3, RR, PE, 1)
+#define SPH_SHIFT_R(D)                                                                  \
+  if (reach == 1) { if (per) { SPH_SHIFT_L##D(1, true); } else { SPH_SHIFT_L##D(1, false); } }      \
+  else if (reach == 2) { if (per) { SPH_SHIFT_L##D(2, true); } else { SPH_SHIFT_L##D(2, false); } } \
+  else { if (per) { SPH_SHIFT_L##D(3, true); } else { SPH_SHIFT_L##D(3, false); } }
   if (kp.dim == 2) {
     SPH_SHIFT_R(2);
   } else {
     SPH_SHIFT_R(3);
   }
 #undef SPH_SHIFT_R
-#undef SPH_SHIFT_P
+#undef SPH_SHIFT_L3
+#undef SPH_SHIFT_L2
 #undef SPH_SHIFT
   return hipGetLastError();
 }

@@ -1,0 +1,58 @@
+"""Shifting with several lanes per target against one lane per target (which it
+takes after an interaction with SPH_INTERACT_ONE_LANE), at a size of each number
+of lanes, with walls, unequal masses and periodic components, on fresh and on
+reused cells.
+
+C sums at most ~400 positive FP32 terms in two orders: within 1e-5 of the
+largest.  The shift sums terms that cancel and is compared, as against the
+oracle, within 1e-4 of the largest shift."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2104_00537_amd import sph as S
+    from test_gpu_lanes import _case
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("option", ["default", "unequal", "periodic"])
+@pytest.mark.parametrize("dim,shape,lo,hi", [(3, (15, 14, 9), 0, 49152),
+                                             (3, (48, 40, 36), 49152, 163840),
+                                             (2, (60, 31), 0, 65536)])
+def test_shifting_lanes_agree_with_one(dim, shape, lo, hi, option):
+    c = _case(dim, shape, option)
+    c.params.shift_coef, c.params.shift_fs = 2.0, 0.9
+    n, P = c.n, S.make_params(c.params)
+    assert lo < n <= hi
+    src, dst = S.DeviceState.from_case(c, DEV), S.DeviceState.empty(dim, n, DEV)
+    key, perm = (torch.empty(n, dtype=torch.int32, device=DEV) for _ in range(2))
+    start = torch.empty(c.params.ncell_total() + 1, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+    S.sph_bin_cells(P, n, src, dst, key, perm, start, ws)
+    t, dt = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+    saved = S.DeviceState.empty(dim, n, DEV, with_type=False, with_id=False)
+    ace, arho = torch.empty((dim, n), device=DEV), torch.empty(n, device=DEV)
+    for reuse in (0, S.SPH_INTERACT_REUSE_CELLS):
+        out = []
+        for one in (0, S.SPH_INTERACT_ONE_LANE):
+            S.sph_interact(P, n, dst, key, start, ace, arho, ws, flags=reuse | one)
+            S.sph_reduce_dt(P, n, dt, ws)
+            keep = dst.pos.clone()
+            conc = torch.full((n,), float("nan"), device=DEV)
+            shift = torch.full((dim, n), float("nan"), device=DEV)
+            S.sph_shifting(P, n, dst, key, start, dt, ws, conc=conc, shift=shift, flags=reuse)
+            moved = dst.pos - keep
+            dst.pos.copy_(keep)
+            out.append((conc, shift, moved))
+        many, single = out
+        assert (many[0] - single[0]).abs().max().item() <= 1e-5 * single[0].abs().max().item()
+        for k in (1, 2):
+            scale = single[k].abs().max().item()
+            assert scale > 0 and (many[k] - single[k]).abs().max().item() <= 1e-4 * scale
+        if not reuse:
+            S.sph_symplectic_step(P, n, 0, dt, t, saved, dst, ace, arho, ws)
+            S.sph_refresh_view(P, n, dst, key, ws)
+    assert S.sph_read_error(ws) == 0
