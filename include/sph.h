@@ -23,6 +23,8 @@
  *                        after each phase of sph_symplectic_step.
  *   sph_shifting         particle shifting (Section 2.8, Eq. 40-41, 53) after
  *                        the corrector.
+ *   sph_interact_conc, sph_shifting_conc   the PI that sums shifting's
+ *                        concentration too, and the shifting with it.
  *   sph_refresh_view     the interaction's view of the half state on the cells
  *                        of the last binning (the n+1/2 PI without a second NL).
  *   sph_build_list,      per-target neighbour lists with a skin, built once per
@@ -503,6 +505,24 @@ sph_status sph_mdbc(const sph_params* p, int64_t n, sph_state* s, const uint32_t
 sph_status sph_shifting(const sph_params* p, int64_t n, sph_state* s, const uint32_t* key,
                         const uint32_t* cell_start, const double* dt, float* conc,
                         float* shift, uint32_t flags, void* ws, size_t ws_bytes, void* stream);
+
+/* sph_interact on reused cells (flags SPH_INTERACT_REUSE_CELLS, with or without
+ * SPH_INTERACT_ONE_LANE) that sums the concentration C of sph_shifting in the
+ * same pass, and the rest of sph_shifting with that C: the same results with one
+ * walk over the neighbours less.
+ *   conc[n]  the C of every particle, written by the first and read by the
+ *            second call; null in both: the workspace's sort buffer, valid
+ *            until the next sph_bin_cells.
+ * For the default formulation (Wendland kernel, artificial viscosity, ddt 0 or
+ * 1), DBC walls, equal masses and no floating bodies; else SPH_E_ARG. */
+sph_status sph_interact_conc(const sph_params* p, int64_t n, const sph_state* s,
+                             const uint32_t* key, const uint32_t* cell_start, float* ace,
+                             float* arho, float* conc, uint32_t flags, void* ws, size_t ws_bytes,
+                             void* stream);
+sph_status sph_shifting_conc(const sph_params* p, int64_t n, sph_state* s, const uint32_t* key,
+                             const uint32_t* cell_start, const double* dt, float* conc,
+                             float* shift, uint32_t flags, void* ws, size_t ws_bytes,
+                             void* stream);
 
 /* Floating bodies (Section 3.2).  A body is a rigid object whose particles
  * are the particles of type SPH_FLOATING with id in [id_first, id_first +

@@ -437,8 +437,43 @@ sph_status sph_shifting(const sph_params* p, int64_t n, sph_state* s, const uint
   if (ws_bytes < ws_layout(n).total) return SPH_E_WORKSPACE;
   if (n == 0) return SPH_OK;
   return hip_status(launch_shifting(make_kparams(*p), n, *s, key, cell_start, dt, conc, shift,
-                                    (flags & SPH_INTERACT_REUSE_CELLS) != 0, ws,
+                                    (flags & SPH_INTERACT_REUSE_CELLS) != 0, false, ws,
                                     (hipStream_t)stream));
+}
+
+// The cases whose interaction on reused cells can sum the concentration too.
+static bool conc_params_ok(const sph_params* p, int64_t n) {
+  return params_ok(p) && n_ok(n) && walk_size_ok(p, n) && p->kernel == 0 && p->viscosity == 0 &&
+         p->ddt != 2 && p->floating == 0 && p->boundary == 0 &&
+         p->mass_fluid == p->mass_bound && periodic_reach_ok(p, p->cell_div + 1);
+}
+
+sph_status sph_interact_conc(const sph_params* p, int64_t n, const sph_state* s,
+                             const uint32_t* key, const uint32_t* cell_start, float* ace,
+                             float* arho, float* conc, uint32_t flags, void* ws, size_t ws_bytes,
+                             void* stream) {
+  if (!conc_params_ok(p, n) || !cell_start || !ws) return SPH_E_ARG;
+  if (n > 0 && (!state_ok(s, true) || !key || !ace || !arho || f64_state(s))) return SPH_E_ARG;
+  if ((flags & ~(uint32_t)SPH_INTERACT_ONE_LANE) != SPH_INTERACT_REUSE_CELLS) return SPH_E_ARG;
+  if (ws_bytes < ws_layout(n).total) return SPH_E_WORKSPACE;
+  if (n == 0)
+    return sph_interact(p, n, s, key, cell_start, ace, arho, nullptr, nullptr, flags, ws, ws_bytes,
+                        stream);
+  return hip_status(launch_interact_conc(make_kparams(*p), n, *s, key, cell_start, ace, arho, conc,
+                                         flags, ws, (hipStream_t)stream));
+}
+
+sph_status sph_shifting_conc(const sph_params* p, int64_t n, sph_state* s, const uint32_t* key,
+                             const uint32_t* cell_start, const double* dt, float* conc,
+                             float* shift, uint32_t flags, void* ws, size_t ws_bytes,
+                             void* stream) {
+  if (!conc_params_ok(p, n) || !cell_start || !dt || !ws) return SPH_E_ARG;
+  if (!(p->shift_coef > 0.0) || flags != SPH_INTERACT_REUSE_CELLS) return SPH_E_ARG;
+  if (n > 0 && (!state_ok(s, true) || !key || f64_state(s))) return SPH_E_ARG;
+  if (ws_bytes < ws_layout(n).total) return SPH_E_WORKSPACE;
+  if (n == 0) return SPH_OK;
+  return hip_status(launch_shifting(make_kparams(*p), n, *s, key, cell_start, dt, conc, shift,
+                                    true, true, ws, (hipStream_t)stream));
 }
 
 int32_t sph_read_error(const void* ws) {

@@ -40,13 +40,14 @@ __device__ __forceinline__ void key_cell(const KParams& kp, uint32_t k, int& cx,
 // LPT lanes per target particle (sorted order): 1 is the production kernel of
 // large cases; more deal each target's rows to that many lanes, for cases too
 // small to fill the GPU (see lanes_per_target).
-template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT>
+template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT, bool CONC = false>
 __global__ __launch_bounds__(kBlock) void k_interact_gather(
     KParams kp, int64_t n, const float4* __restrict__ pr, const float4* __restrict__ vp,
     const uint32_t* __restrict__ key, const uint32_t* __restrict__ cstart,
     const uint8_t* __restrict__ type, const double* __restrict__ pos64, float* __restrict__ ace,
     float* __restrict__ arho, float* __restrict__ visc, uint32_t* __restrict__ nbr,
-    BlockRed* __restrict__ red, WsHeader* __restrict__ hdr, const uint32_t* __restrict__ disp) {
+    BlockRed* __restrict__ red, WsHeader* __restrict__ hdr, const uint32_t* __restrict__ disp,
+    float* __restrict__ conc) {
   static_assert(LPT >= 1 && LPT <= kMaxLanes && (LPT & (LPT - 1)) == 0, "a power of two");
   const int64_t t = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   const int64_t i = t / LPT;
@@ -91,15 +92,17 @@ __global__ __launch_bounds__(kBlock) void k_interact_gather(
         const uint32_t rest = k / (uint32_t)kp.ncx;
         const int cy = (int)(rest % (uint32_t)kp.ncy);
         const int cz = (int)(rest / (uint32_t)kp.ncy);
-        gather_walk<DIM, R, DIAG, EQM, GEN, PER>(kp, 0u, n, i, pa, T, cx, cy, cz, pr, vp, cstart,
-                                                pos64, acc, c64, cull2);
+        gather_walk<DIM, R, DIAG, EQM, GEN, PER, 1, CONC>(kp, 0u, n, i, pa, T, cx, cy, cz, pr, vp,
+                                                          cstart, pos64, acc, c64, cull2);
         if (T.fluid) acc.cnt -= 1u;  // the self pair: counted, added nothing
         const uint32_t c = DIAG ? c64 : acc.cnt;
         write_target<DIM>(kp, n, i, T, acc, c, ace, arho, visc, nbr, fmag, vmax_out, nfl);
+        if (CONC) conc[i] = conc_scale(kp) * acc.conc;
         cnt_out = acc.cnt;
         cnt_wall = T.fluid ? 0u : acc.cnt;
       } else {
         write_zero<DIM>(n, i, ace, arho, visc, nbr);
+        if (CONC) conc[i] = 0.f;
       }
     }
   } else {
@@ -113,19 +116,22 @@ __global__ __launch_bounds__(kBlock) void k_interact_gather(
       const float4 pa = pr[i];
       int cx, cy, cz;
       key_cell(kp, key[i], cx, cy, cz);
-      gather_walk<DIM, R, DIAG, EQM, GEN, PER, LPT>(kp, 0u, n, i, pa, T, cx, cy, cz, pr, vp,
-                                                    cstart, pos64, acc, c64, cull2, sub);
+      gather_walk<DIM, R, DIAG, EQM, GEN, PER, LPT, CONC>(kp, 0u, n, i, pa, T, cx, cy, cz, pr,
+                                                          vp, cstart, pos64, acc, c64, cull2,
+                                                          sub);
     }
-    combine_lanes<LPT>(acc, c64);  // every lane: the sums of its target's lanes
+    combine_lanes<LPT, CONC>(acc, c64);  // every lane: the sums of its target's lanes
     if (i < n && sub == 0) {
       if (active) {
         if (T.fluid) acc.cnt -= 1u;  // the self pair: counted, added nothing
         const uint32_t c = DIAG ? c64 : acc.cnt;
         write_target<DIM>(kp, n, i, T, acc, c, ace, arho, visc, nbr, fmag, vmax_out, nfl);
+        if (CONC) conc[i] = conc_scale(kp) * acc.conc;
         cnt_out = acc.cnt;
         cnt_wall = T.fluid ? 0u : acc.cnt;
       } else {
         write_zero<DIM>(n, i, ace, arho, visc, nbr);
+        if (CONC) conc[i] = 0.f;
       }
     }
   }
@@ -168,7 +174,7 @@ hipError_t launch_gather(const KParams& kp, int64_t n, const sph_state& s, const
   hipLaunchKernelGGL((k_interact_gather<D, RR, G, PP, GG, PE, LP>),                           \
                      dim3(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u),           \
                      dim3(kBlock), 0, st, kp, n, w.pr, w.vp, key, cell_start, s.type, s.pos, ace, \
-                     arho, visc, nbr, w.red, w.hdr, w.disp)
+                     arho, visc, nbr, w.red, w.hdr, w.disp, nullptr)
 // The formulation and the periodic components are chosen apart: the general pair
 // terms test the case's options for every pair, which a periodic case in the
 // default formulation need not pay (958k particles in a periodic channel:

@@ -17,6 +17,7 @@ struct PairAcc {
   float diff;        // density diffusion sum = kfab m_f * diff
   float vmax;        // visc = h * vmax
   uint32_t cnt;      // pairs evaluated
+  float conc;        // CONC: the concentration of Eq. 53, C_a = m w_alpha * conc
 };
 
 struct TargetData {
@@ -34,6 +35,15 @@ __device__ __forceinline__ float max_abs(float m, float t) {
   float r;
   asm("v_max_f32_e64 %0, %1, |%2|" : "=v"(r) : "v"(m), "v"(t));
   return r;
+}
+
+// C_a of a sum of V_b W_ab / (m_f w_alpha).
+__device__ __forceinline__ float conc_scale(const KParams& kp) {
+  return (float)kp.mass_f * kp.w_alpha_f;
+}
+// c + V_b W_ab / (m_f w_alpha) for Wendland C2 with w = 1 - q/2 and fv = w^3 / rho_b.
+__device__ __forceinline__ float conc_wendland(float fv, float w, float c) {
+  return fmaf(fv * w, fmaf(-4.f, w, 5.f), c);
 }
 
 // The pair terms of Eq. 15, 17-18, 21-22 and 36 for one pair (a, b) with
@@ -65,7 +75,12 @@ __device__ __forceinline__ float max_abs(float m, float t) {
 // default formulation (Wendland C2, artificial viscosity, Eq. 18 or no
 // diffusion), whose code keeps the register budget of the production pass.
 // EQM: fluid and wall particles have the same mass (mr = 1 for every pair).
-template <int DIM, bool EQM, bool GEN>
+// CONC (the default formulation with equal masses): also the concentration
+// C_a = sum_b V_b W_ab that particle shifting needs, over every neighbour; the
+// pairs of two walls (passed in this form only) take part in it alone.  With
+// w = 1 - q/2, W_ab = w_alpha w^4 (2q + 1) = w_alpha g w (5 - 4w): three
+// operations on what the pair has at hand (conc_wendland has the same ones).
+template <int DIM, bool EQM, bool GEN, bool CONC = false>
 __device__ __forceinline__ void pair_terms(const KParams& kp, const TargetData& a, float dx,
                                            float dy, float dz, float r2, float pbw,
                                            const float4& vb, PairAcc& acc) {
@@ -75,9 +90,10 @@ __device__ __forceinline__ void pair_terms(const KParams& kp, const TargetData& 
   // (explicit fused multiply-adds: the same bits in every kernel)
   const float vr = DIM == 3 ? fmaf(dvz, dz, fmaf(dvy, dy, dvx * dx)) : fmaf(dvy, dy, dvx * dx);
   const float s = __builtin_amdgcn_sqrtf(r2);
-  float g;
+  static_assert(!CONC || (EQM && !GEN), "C in the default formulation with equal masses");
+  float g, w = 0.f;
   if (!GEN || kp.kernel == 0) {
-    const float w = fmaf(s, kp.mhalf_inv_h_f, 1.f);  // 1 - q/2
+    w = fmaf(s, kp.mhalf_inv_h_f, 1.f);  // 1 - q/2
     g = w * w * w;
   } else {
     const float q = s * kp.inv_h_f, u = 2.f - q;
@@ -85,8 +101,15 @@ __device__ __forceinline__ void pair_terms(const KParams& kp, const TargetData& 
   }
   if (!EQM && !fb) g *= kp.mass_ratio_f;  // m_b / m_f for a wall neighbour
   const float fv = g * __builtin_amdgcn_rcpf(rhob);
-  acc.cont = fmaf(fv, vr, acc.cont);
-  acc.cnt += 1u;
+  if (CONC) {
+    acc.conc = conc_wendland(fv, w, acc.conc);
+    const bool real = a.fluid || fb;  // (not two walls)
+    acc.cont = fmaf(real ? fv : 0.f, vr, acc.cont);
+    acc.cnt += real ? 1u : 0u;
+  } else {
+    acc.cont = fmaf(fv, vr, acc.cont);
+    acc.cnt += 1u;
+  }
   if (a.fluid || (GEN && a.flt)) {
     const float rr = __builtin_amdgcn_rcpf(r2 + kp.eta2_f);
     const float t = vr * rr;
@@ -255,7 +278,7 @@ __device__ __forceinline__ void load_group(const float4* __restrict__ pr, uint32
 // period, which exceeds twice the reach of the stencil.  Along y and z the
 // offsets are cell-relative and (ys, zs) carry the row's cell shift.  Wall
 // targets skip wall candidates (Eq. 36).
-template <int DIM, bool DIAG, bool EQM, bool GEN, bool PER, int NU = 4>
+template <int DIM, bool DIAG, bool EQM, bool GEN, bool PER, int NU = 4, bool CONC = false>
 __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64_t i,
                                              uint32_t xa, float ys, float zs,
                                              const TargetData& T, uint32_t o,
@@ -271,7 +294,7 @@ __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64
 #pragma unroll
   for (int u = 0; u < NU; ++u) {
     r2s[u] = pair_geom<DIM>(kp, xa, ys, zs, pb[u], dxs[u], dys[u], dzs[u]);
-    hit[u] = (T.fluid || pb[u].w > 0.f) && r2s[u] < kp.support2_f;
+    hit[u] = (CONC || T.fluid || pb[u].w > 0.f) && r2s[u] < kp.support2_f;
     if (DIAG) {
       const uint32_t jj = (o >> 4) + u;
       // (pb.w == 0: a particle excluded by a view refresh, no neighbour)
@@ -298,7 +321,7 @@ __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64
 #pragma unroll
   for (int u = 0; u < NU; ++u)
     if (hit[u])
-      pair_terms<DIM, EQM, GEN>(kp, T, dxs[u], dys[u], dzs[u], r2s[u], pb[u].w, vb[u], acc);
+      pair_terms<DIM, EQM, GEN, CONC>(kp, T, dxs[u], dys[u], dzs[u], r2s[u], pb[u].w, vb[u], acc);
 }
 
 // The candidate walk of one target lane over the rows of its neighbour cells
@@ -428,7 +451,7 @@ __device__ __forceinline__ void walk_rows(const KParams& kp, uint32_t cbase, con
 // the caller takes it off the count (fluid targets meet themselves; wall
 // targets skip wall candidates).  DIAG also counts neighbours with an FP64
 // test on the FP64 positions (c64, self excluded).
-template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT = 1>
+template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT = 1, bool CONC = false>
 __device__ __forceinline__ void gather_walk(const KParams& kp, uint32_t cbase, int64_t n,
                                             int64_t i, const float4& pa, const TargetData& T,
                                             int cx, int cy, int cz,
@@ -442,16 +465,16 @@ __device__ __forceinline__ void gather_walk(const KParams& kp, uint32_t cbase, i
     for (int d = 0; d < DIM; ++d) pa64[d] = pos64[d * n + i];
   auto walk = [&](uint32_t o, uint32_t o1, uint32_t xv, float ys, float zs) {
     for (; o + 64u <= o1; o += 64u)
-      gather_group<DIM, DIAG, EQM, GEN, PER>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64, pos64, acc,
-                                             c64);
+      gather_group<DIM, DIAG, EQM, GEN, PER, 4, CONC>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64,
+                                                      pos64, acc, c64);
     if (o + 32u <= o1) {
-      gather_group<DIM, DIAG, EQM, GEN, PER, 2>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64, pos64,
-                                                acc, c64);
+      gather_group<DIM, DIAG, EQM, GEN, PER, 2, CONC>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64,
+                                                      pos64, acc, c64);
       o += 32u;
     }
     if (o < o1)
-      gather_group<DIM, DIAG, EQM, GEN, PER, 1>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64, pos64,
-                                                acc, c64);
+      gather_group<DIM, DIAG, EQM, GEN, PER, 1, CONC>(kp, n, i, xv, ys, zs, T, o, pr, vp, pa64,
+                                                      pos64, acc, c64);
   };
   walk_rows<DIM, R, PER, LPT>(kp, cbase, pa, cx, cy, cz, cstart, cull2, sub, LPT, walk);
 }
@@ -459,7 +482,7 @@ __device__ __forceinline__ void gather_walk(const KParams& kp, uint32_t cbase, i
 // Sums the walks of the LPT lanes of each target (adjacent lanes, LPT a
 // power of two); every lane of the wave calls this, and every lane of a
 // group ends with the group's sums.  Maxima take the maximum.
-template <int LPT>
+template <int LPT, bool CONC = false>
 __device__ __forceinline__ void combine_lanes(PairAcc& acc, uint32_t& c64) {
   for (int off = 1; off < LPT; off <<= 1) {
     acc.ax += __shfl_xor(acc.ax, off, 64);
@@ -470,6 +493,7 @@ __device__ __forceinline__ void combine_lanes(PairAcc& acc, uint32_t& c64) {
     acc.vmax = fmaxf(acc.vmax, __shfl_xor(acc.vmax, off, 64));
     acc.cnt += (uint32_t)__shfl_xor((int)acc.cnt, off, 64);
     c64 += (uint32_t)__shfl_xor((int)c64, off, 64);
+    if (CONC) acc.conc += __shfl_xor(acc.conc, off, 64);
   }
 }
 

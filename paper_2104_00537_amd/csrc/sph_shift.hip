@@ -14,17 +14,22 @@
 
 namespace sph {
 
-// W(r) / w_alpha of the case's kernel: Wendland C2 (Eq. 11) (1 - q/2)^4 (2q + 1)
-// or cubic spline (Eq. 10).
-__device__ inline float kernel_w_f(const KParams& kp, float r2) {
-  const float q = __builtin_amdgcn_sqrtf(r2) * kp.inv_h_f;
-  if (kp.kernel == 0) {
-    const float w = fmaf(-0.5f, q, 1.f), ww = w * w;
-    return ww * ww * fmaf(2.f, q, 1.f);
-  }
+// W / w_alpha of the cubic spline (Eq. 10).
+__device__ inline float spline_w_f(float q) {
   if (q <= 1.f) return fmaf(q * q, fmaf(0.75f, q, -1.5f), 1.f);
   const float u = 2.f - q;
   return 0.25f * u * u * u;
+}
+
+// c + vb W(r) / w_alpha for the case's kernel: Wendland C2 (Eq. 11), with the
+// operations of the interaction's own sum (pair_terms), or cubic spline (Eq. 10).
+__device__ inline float add_conc(const KParams& kp, float r2, float vb, float c) {
+  const float s = __builtin_amdgcn_sqrtf(r2);
+  if (kp.kernel == 0) {
+    const float w = fmaf(s, kp.mhalf_inv_h_f, 1.f);
+    return conc_wendland(w * w * w * vb, w, c);
+  }
+  return fmaf(vb, spline_w_f(s * kp.inv_h_f), c);
 }
 
 // F_ab / kfab with grad_a W_ab = F_ab r_ab (as in the interaction's pair terms).
@@ -86,7 +91,7 @@ __device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, floa
       acc.s[1 % (GRAD ? DIM : 1)] = fmaf(w, dys[u], acc.s[1 % (GRAD ? DIM : 1)]);
       if (DIM == 3) acc.s[2 % (GRAD ? DIM : 1)] = fmaf(w, dzs[u], acc.s[2 % (GRAD ? DIM : 1)]);
     } else {
-      acc.s[0] = fmaf(vb, kernel_w_f(kp, r2s[u]), acc.s[0]);
+      acc.s[0] = add_conc(kp, r2s[u], vb, acc.s[0]);
     }
   }
 }
@@ -174,7 +179,7 @@ __device__ inline float conc_one(const KParams& kp, bool live, uint32_t cbase, i
     acc = shift_walk<DIM, R, PER, false, LPT>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
                                               nullptr, 0.f, sub, lanes);
   }
-  return ((float)kp.mass_f * kp.w_alpha_f) * lanes_sum(acc.s[0], lanes);
+  return conc_scale(kp) * lanes_sum(acc.s[0], lanes);
 }
 
 // grad C_a = sum_b V_b (C_b - C_a) F_ab r_ab and dr_a = -A_s h |v_a| dt grad C_a
@@ -347,7 +352,7 @@ static int shift_lanes(int dim, int64_t n) {
 
 hipError_t launch_shifting(const KParams& kp, int64_t n, const sph_state& s, const uint32_t* key,
                            const uint32_t* cell_start, const double* dt, float* conc,
-                           float* shift, bool reuse, void* ws, hipStream_t st) {
+                           float* shift, bool reuse, bool given, void* ws, hipStream_t st) {
   const WsLayout L = ws_layout(n);
   const float4* pr = ws_ptr<float4>(ws, L.view_pr);
   const float4* vp = ws_ptr<float4>(ws, L.view_vp);
@@ -361,8 +366,9 @@ hipError_t launch_shifting(const KParams& kp, int64_t n, const sph_state& s, con
 #define SPH_SHIFT(D, RR, PE, LP)                                                              \
   do {                                                                                        \
     const dim3 grid(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u);                 \
-    hipLaunchKernelGGL((k_shift_conc<D, RR, PE, LP>), grid, dim3(kBlock), 0, st, kp, n, pr,   \
-                       key, cell_start, s.type, c, disp, hdr);                                \
+    if (!given)                                                                               \
+      hipLaunchKernelGGL((k_shift_conc<D, RR, PE, LP>), grid, dim3(kBlock), 0, st, kp, n, pr, \
+                         key, cell_start, s.type, c, disp, hdr);                              \
     hipLaunchKernelGGL((k_shift_apply<D, RR, PE, LP>), grid, dim3(kBlock), 0, st, kp, n,      \
                        pr, vp, key, cell_start, s.type, c, dt, s.pos, shift, disp, hdr);      \
   } while (0)

@@ -120,6 +120,14 @@ class Simulation:
             raise ValueError("neighbour lists need the reused-cells step with the default "
                              "formulation, DBC walls and no floating bodies, shifting or "
                              "periodic components")
+        # shifting's concentration summed by the second interaction (where
+        # sph_interact_conc takes the case)
+        self.fused_conc = (self.shifting and self.reuse_cells
+                           and (self.flags & ~S.SPH_INTERACT_ONE_LANE) == 0
+                           and int(getattr(cp, "kernel", 0)) == 0
+                           and int(getattr(cp, "viscosity", 0)) == 0 and int(cp.ddt) != 2
+                           and int(getattr(cp, "floating", 0)) == 0
+                           and cp.mass_fluid == cp.mass_bound)
         self.neighbour_list = bool(neighbour_list)
         self.list = None
         if self.neighbour_list:
@@ -251,6 +259,9 @@ class Simulation:
             call("interact", S.sph_interact_list, P, n, b, self.key, self.cell_start, self.list,
                  self.ace, self.arho, self.ws, flags=self.flags | S.SPH_INTERACT_REUSE_CELLS,
                  stream=stream)
+        elif fused and self.fused_conc:
+            S.sph_interact_conc(P, n, b, self.key, self.cell_start, self.ace, self.arho, self.ws,
+                                flags=self.flags | S.SPH_INTERACT_REUSE_CELLS, stream=stream)
         else:
             call("interact", S.sph_interact, P, n, b, self.key, self.cell_start, self.ace,
                  self.arho, self.ws, flags=self.flags | S.SPH_INTERACT_REUSE_CELLS,
@@ -266,7 +277,10 @@ class Simulation:
             if self.bodies is not None:
                 call("floating", S.sph_floating_step, P, n, 1, self.dt, self.bodies, s0, b, self.ace,
                      self.ws, stream=stream)
-        if self.shifting:
+        if fused and self.fused_conc:
+            S.sph_shifting_conc(P, n, b, self.key, self.cell_start, self.dt, self.ws,
+                                stream=stream)
+        elif self.shifting:
             call("shifting", S.sph_shifting, P, n, b, self.key, self.cell_start, self.dt, self.ws,
                  flags=S.SPH_INTERACT_REUSE_CELLS, stream=stream)
         self.states = [b, a]

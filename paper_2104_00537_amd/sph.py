@@ -36,7 +36,7 @@ EXPORTS = ("sph_workspace_bytes", "sph_bin_cells", "sph_refresh_view", "sph_inte
            "sph_interact_noalloc", "sph_list_bytes", "sph_build_list", "sph_interact_list",
            "sph_list_walks", "sph_reduce_dt",
            "sph_symplectic_step", "sph_symplectic_update", "sph_verlet_step", "sph_mdbc", "sph_floating_step",
-           "sph_shifting",
+           "sph_shifting", "sph_interact_conc", "sph_shifting_conc",
            "sph_read_error", "sph_clear_error", "sph_strerror",
            "sph_batch_table_bytes", "sph_batch_describe", "sph_batch_workspace_bytes",
            "sph_batch_bin_cells", "sph_batch_interact", "sph_batch_refresh_view",
@@ -141,6 +141,11 @@ def _load() -> C.CDLL:
     L.sph_shifting.restype = C.c_int32
     L.sph_shifting.argtypes = [P(SphParams), C.c_int64, P(SphState), VP, VP, VP, VP, VP,
                                C.c_uint32, VP, C.c_size_t, VP]
+    L.sph_interact_conc.restype = C.c_int32
+    L.sph_interact_conc.argtypes = [P(SphParams), C.c_int64, P(SphState), VP, VP, VP, VP, VP,
+                                    C.c_uint32, VP, C.c_size_t, VP]
+    L.sph_shifting_conc.restype = C.c_int32
+    L.sph_shifting_conc.argtypes = L.sph_shifting.argtypes
     L.sph_read_error.restype = C.c_int32
     L.sph_read_error.argtypes = [VP]
     L.sph_clear_error.restype = C.c_int32
@@ -430,6 +435,24 @@ def sph_shifting(params: SphParams, n: int, s: DeviceState, key: torch.Tensor,
     _check(lib.sph_shifting(C.byref(params), int(n), C.byref(s.c()), _ptr(key), _ptr(cell_start),
                             _ptr(dt), _ptr(conc), _ptr(shift), int(flags), _ptr(ws), ws.numel(),
                             _stream(stream)), "sph_shifting")
+
+
+def sph_interact_conc(params: SphParams, n: int, s: DeviceState, key: torch.Tensor,
+                      cell_start: torch.Tensor, ace: torch.Tensor, arho: torch.Tensor,
+                      ws: torch.Tensor, conc: Optional[torch.Tensor] = None,
+                      flags: int = SPH_INTERACT_REUSE_CELLS, stream=None):
+    _check(lib.sph_interact_conc(C.byref(params), int(n), C.byref(s.c()), _ptr(key),
+                                 _ptr(cell_start), _ptr(ace), _ptr(arho), _ptr(conc), int(flags),
+                                 _ptr(ws), ws.numel(), _stream(stream)), "sph_interact_conc")
+
+
+def sph_shifting_conc(params: SphParams, n: int, s: DeviceState, key: torch.Tensor,
+                      cell_start: torch.Tensor, dt: torch.Tensor, ws: torch.Tensor,
+                      conc: Optional[torch.Tensor] = None, shift: Optional[torch.Tensor] = None,
+                      flags: int = SPH_INTERACT_REUSE_CELLS, stream=None):
+    _check(lib.sph_shifting_conc(C.byref(params), int(n), C.byref(s.c()), _ptr(key),
+                                 _ptr(cell_start), _ptr(dt), _ptr(conc), _ptr(shift), int(flags),
+                                 _ptr(ws), ws.numel(), _stream(stream)), "sph_shifting_conc")
 
 
 def sph_read_error(ws: torch.Tensor) -> int:

@@ -56,3 +56,58 @@ def test_shifting_lanes_agree_with_one(dim, shape, lo, hi, option):
             S.sph_symplectic_step(P, n, 0, dt, t, saved, dst, ace, arho, ws)
             S.sph_refresh_view(P, n, dst, key, ws)
     assert S.sph_read_error(ws) == 0
+
+
+@pytest.mark.parametrize("option", ["default", "periodic"])
+@pytest.mark.parametrize("dim,shape", [(3, (15, 14, 9)), (3, (34, 32, 26)), (3, (48, 40, 36)),
+                                       (3, (60, 60, 50)), (3, (80, 72, 68)), (2, (60, 31)),
+                                       (2, (260, 200)), (2, (420, 320))])
+def test_concentration_of_the_interaction(dim, shape, option):
+    """C summed by the interaction (sph_interact_conc) and the shifting with it
+    against the separate calls, at a size of each number of lanes.  The rates
+    and pair counts take the same operations in the same order and C the same
+    operations in the order of its lanes: rates within a rounding of their
+    largest (1e-6), C and shifts as above."""
+    c = _case(dim, shape, option)
+    c.params.shift_coef, c.params.shift_fs = 2.0, 0.9
+    n, P = c.n, S.make_params(c.params)
+    src, dst = S.DeviceState.from_case(c, DEV), S.DeviceState.empty(dim, n, DEV)
+    key, perm = (torch.empty(n, dtype=torch.int32, device=DEV) for _ in range(2))
+    start = torch.empty(c.params.ncell_total() + 1, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+    S.sph_bin_cells(P, n, src, dst, key, perm, start, ws)
+    t, dt = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+    saved = S.DeviceState.empty(dim, n, DEV, with_type=False, with_id=False)
+    ace, arho = torch.empty((dim, n), device=DEV), torch.empty(n, device=DEV)
+    S.sph_interact(P, n, dst, key, start, ace, arho, ws)
+    S.sph_reduce_dt(P, n, dt, ws)
+    S.sph_symplectic_step(P, n, 0, dt, t, saved, dst, ace, arho, ws)
+    S.sph_refresh_view(P, n, dst, key, ws)
+    reuse = S.SPH_INTERACT_REUSE_CELLS
+    for lanes in (0, S.SPH_INTERACT_ONE_LANE):
+        out = []
+        for fused in (True, False):
+            ace, arho, conc = (torch.full(s, float("nan"), device=DEV)
+                               for s in ((dim, n), (n,), (n,)))
+            shift = torch.full((dim, n), float("nan"), device=DEV)
+            inter = torch.zeros(2, dtype=torch.int64, device=DEV)
+            half = torch.zeros(1, dtype=torch.float64, device=DEV)
+            keep = dst.pos.clone()
+            if fused:
+                S.sph_interact_conc(P, n, dst, key, start, ace, arho, ws, conc=conc,
+                                    flags=reuse | lanes)
+                S.sph_shifting_conc(P, n, dst, key, start, dt, ws, conc=conc, shift=shift)
+            else:
+                S.sph_interact(P, n, dst, key, start, ace, arho, ws, flags=reuse | lanes)
+                S.sph_shifting(P, n, dst, key, start, dt, ws, conc=conc, shift=shift, flags=reuse)
+            S.sph_reduce_dt(P, n, half, ws, interactions=inter)
+            dst.pos.copy_(keep)
+            out.append((ace, arho, conc, shift, inter, half))
+        a, b = out
+        assert torch.equal(a[4], b[4]) and abs(a[5].item() - b[5].item()) <= 1e-6 * b[5].item()
+        for k, tol in ((0, 1e-6), (1, 1e-6), (2, 1e-5), (3, 1e-4)):
+            scale = b[k].abs().max().item()
+            assert scale > 0 and (a[k] - b[k]).abs().max().item() <= tol * scale, k
+        if lanes:
+            assert torch.equal(a[2], b[2])
+    assert S.sph_read_error(ws) == 0
