@@ -37,11 +37,28 @@ __device__ __forceinline__ void key_cell(const KParams& kp, uint32_t k, int& cx,
   cz = (int)(rest / (uint32_t)kp.ncy);
 }
 
+// Wavefronts per SIMD that the registers are held to (1: not held).  The walk
+// fills its waits with other wavefronts, and a case of few rounds of wavefronts
+// ends on a partly filled one, so that one more or less per SIMD shows (us per
+// pass; R = 2 / 3):
+//   2-D, 503k: 7 (by its scalar registers) 66.6 / 66.1, 8: 56.0 / 55.3; larger
+//     and smaller cases within 2 % either way
+//   3-D, 1.32M: 7 573 / 576, 8 (it spills) 591 / 593; 1.58M: 699 / 703, 723 / 723
+//   3-D periodic, 958k: 6 604 / 610, 7 574 / 579, 8 621 / 630
+//   3-D with options, 441k: 5 304 / 307, 6 266 / 268, 7 271 / 272
+// With several lanes per target the better number changes with the size (2 lanes:
+// 223k 124 at 6 and 128 at 7, 294k 180 and 167): left to the compiler.
+constexpr int gather_waves(int dim, bool plain, bool gen, int lpt) {
+  if (!plain || (dim == 2 && gen) || (dim == 3 && lpt > 1)) return 1;
+  return dim == 2 ? 8 : gen ? 6 : 7;
+}
+
 // LPT lanes per target particle (sorted order): 1 is the production kernel of
 // large cases; more deal each target's rows to that many lanes, for cases too
 // small to fill the GPU (see lanes_per_target).
 template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT, bool CONC = false>
-__global__ __launch_bounds__(kBlock) void k_interact_gather(
+__global__ __launch_bounds__(kBlock, gather_waves(DIM, EQM && !DIAG, GEN, LPT)) void
+k_interact_gather(
     KParams kp, int64_t n, const float4* __restrict__ pr, const float4* __restrict__ vp,
     const uint32_t* __restrict__ key, const uint32_t* __restrict__ cstart,
     const uint8_t* __restrict__ type, const double* __restrict__ pos64, float* __restrict__ ace,

@@ -91,9 +91,9 @@ __device__ __forceinline__ void pair_terms(const KParams& kp, const TargetData& 
   const float vr = DIM == 3 ? fmaf(dvz, dz, fmaf(dvy, dy, dvx * dx)) : fmaf(dvy, dy, dvx * dx);
   const float s = __builtin_amdgcn_sqrtf(r2);
   static_assert(!CONC || (EQM && !GEN), "C in the default formulation with equal masses");
-  float g, w = 0.f;
+  float g;
   if (!GEN || kp.kernel == 0) {
-    w = fmaf(s, kp.mhalf_inv_h_f, 1.f);  // 1 - q/2
+    const float w = fmaf(s, kp.mhalf_inv_h_f, 1.f);  // 1 - q/2
     g = w * w * w;
   } else {
     const float q = s * kp.inv_h_f, u = 2.f - q;
@@ -102,7 +102,7 @@ __device__ __forceinline__ void pair_terms(const KParams& kp, const TargetData& 
   if (!EQM && !fb) g *= kp.mass_ratio_f;  // m_b / m_f for a wall neighbour
   const float fv = g * __builtin_amdgcn_rcpf(rhob);
   if (CONC) {
-    acc.conc = conc_wendland(fv, w, acc.conc);
+    acc.conc = conc_wendland(fv, fmaf(s, kp.mhalf_inv_h_f, 1.f), acc.conc);
     const bool real = a.fluid || fb;  // (not two walls)
     acc.cont = fmaf(real ? fv : 0.f, vr, acc.cont);
     acc.cnt += real ? 1u : 0u;
