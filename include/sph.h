@@ -606,8 +606,8 @@ enum {
    * (type SPH_EXCLUDED) to get it. */
   SPH_BATCH_WAVE_ALIGNED = 1u,
   /* also an option of sph_batch_describe: in a wave-aligned batch, a slot of
-   * at most 131,072 particles gets four lanes per target (as the
-   * single-case pass does for small cases), the others one.  The choice depends
+   * at most 131,072 particles gets four lanes per target (the
+   * single-case pass chooses 1 to 16 by size), the others one.  The choice depends
    * on the option and the slot's own size only, so a case's results do not
    * depend on the other slots.  It shortens each target's chain of loads,
    * which pays when the batch is too small to fill the GPU; when it fills
