@@ -160,6 +160,14 @@ constexpr int kMaxLanes = 16;
 constexpr int kBatchLanes = 4;
 constexpr int64_t kBatchLanesMaxN = 131072;
 
+// Whether the walk over the rows of a case of n particles on a grid of `cells`
+// cells can take 32-bit byte offsets: 16 bytes per particle in the views, with
+// room for the group of 4 that a range's end is tested with, and 4 per entry of
+// the cell ranges (`cells` + 1 of them).
+inline bool walk_fits_32(int64_t n, uint64_t cells) {
+  return n < ((int64_t)1 << 28) - 4 && cells < ((uint64_t)1 << 30);
+}
+
 // Workspace layout (offsets in bytes, each region 256-aligned).
 struct WsLayout {
   size_t err;        // the WsHeader (offset 0)

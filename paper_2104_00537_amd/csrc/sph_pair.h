@@ -251,15 +251,16 @@ __device__ __forceinline__ const T& at32(const T* __restrict__ base, uint32_t k)
                                      (uint32_t)(k * (uint32_t)sizeof(T)));
 }
 // The element U places after byte offset o (U a compile-time constant, folded
-// into the load's immediate offset).
-template <int U, typename T>
-__device__ __forceinline__ const T& at_byte(const T* __restrict__ base, uint32_t o) {
+// into the load's immediate offset; O: 32 bits, or 64 for the walks of cases
+// beyond walk_fits_32).
+template <int U, typename T, typename O>
+__device__ __forceinline__ const T& at_byte(const T* __restrict__ base, O o) {
   return *(reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + o) + U);
 }
 
 // The positions of NU consecutive candidates from byte offset o of the view.
-template <int NU>
-__device__ __forceinline__ void load_group(const float4* __restrict__ pr, uint32_t o,
+template <int NU, typename O>
+__device__ __forceinline__ void load_group(const float4* __restrict__ pr, O o,
                                            float4 (&pb)[NU]) {
   pb[0] = at_byte<0>(pr, o);
   if (NU > 1) pb[1 % NU] = at_byte<1>(pr, o);
@@ -362,8 +363,9 @@ __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64
 //
 // walk(o, o1, xv, ys, zs) is called for every candidate range: byte offsets o to
 // o1 in the views, the target's x bits xv and its offsets (ys, zs) in the
-// range's frame.
-template <int DIM, int R, bool PER, int LPT, typename Walk>
+// range's frame.  WIDE: 64-bit offsets and indices, for a case beyond
+// walk_fits_32.
+template <int DIM, int R, bool PER, int LPT, bool WIDE = false, typename Walk>
 __device__ __forceinline__ void walk_rows(const KParams& kp, uint32_t cbase, const float4& pa,
                                           int cx, int cy, int cz,
                                           const uint32_t* __restrict__ cstart, float cull2,
@@ -413,7 +415,10 @@ __device__ __forceinline__ void walk_rows(const KParams& kp, uint32_t cbase, con
     const float ys = row_shift(pa.y, dy, cs), zs = row_shift(pa.z, dz, cs);
     // the candidates of key cells [c0, c1] of the row, with target x bits xv
     auto range = [&](int c0, int c1, uint32_t xv) {
-      walk(at32(cstart, row + c0) * 16u, at32(cstart, row + c1 + 1) * 16u, xv, ys, zs);
+      if constexpr (WIDE)
+        walk((uint64_t)cstart[row + c0] * 16u, (uint64_t)cstart[row + c1 + 1] * 16u, xv, ys, zs);
+      else
+        walk(at32(cstart, row + c0) * 16u, at32(cstart, row + c1 + 1) * 16u, xv, ys, zs);
     };
     if (perx) {
       if (x0 < 0) {  // cells at the far end, one period below

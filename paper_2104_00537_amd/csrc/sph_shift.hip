@@ -54,9 +54,9 @@ struct ShiftAcc {
 // gather_group): positions loaded together and tested, then for the gradient
 // the concentrations of the hits, then their terms.  LAST: only the candidates
 // before byte offset o1 count (the view is padded by kViewPad entries).
-template <int DIM, bool GRAD, bool LAST>
+template <int DIM, bool GRAD, bool LAST, typename O>
 __device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, float ys, float zs,
-                                            uint32_t o, uint32_t o1, const float4* __restrict__ pr,
+                                            O o, O o1, const float4* __restrict__ pr,
                                             const float* __restrict__ conc, float ca,
                                             ShiftAcc<DIM, GRAD>& acc) {
   constexpr int NU = 4;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, floa
   }
   float cb[NU];
   if (GRAD) {
-    const uint32_t oc = o >> 2;
+    const O oc = o >> 2;
     if (hit[0]) cb[0] = at_byte<0>(conc, oc);
     if (hit[1]) cb[1] = at_byte<1>(conc, oc);
     if (hit[2]) cb[2] = at_byte<2>(conc, oc);
@@ -99,7 +99,7 @@ __device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, floa
 // The sums of one target (view position pa, key cell (cx, cy, cz), cell keys
 // offset by cbase) over the rows of lane `sub` of its LPT (walk_rows): each
 // range as whole groups of 4 and a masked one.
-template <int DIM, int R, bool PER, bool GRAD, int LPT>
+template <int DIM, int R, bool PER, bool GRAD, int LPT, bool WIDE>
 __device__ __forceinline__ ShiftAcc<DIM, GRAD> shift_walk(const KParams& kp, uint32_t cbase,
                                                const float4& pa, int cx, int cy, int cz,
                                                const float4* __restrict__ pr,
@@ -107,12 +107,12 @@ __device__ __forceinline__ ShiftAcc<DIM, GRAD> shift_walk(const KParams& kp, uin
                                                const float* __restrict__ conc, float ca,
                                                int sub, int stride) {
   ShiftAcc<DIM, GRAD> acc{};
-  auto walk = [&](uint32_t o, uint32_t o1, uint32_t xv, float ys, float zs) {
+  auto walk = [&](auto o, auto o1, uint32_t xv, float ys, float zs) {
     for (; o + 64u <= o1; o += 64u)
       shift_group<DIM, GRAD, false>(kp, xv, ys, zs, o, o1, pr, conc, ca, acc);
     if (o < o1) shift_group<DIM, GRAD, true>(kp, xv, ys, zs, o, o1, pr, conc, ca, acc);
   };
-  walk_rows<DIM, R, PER, LPT>(kp, cbase, pa, cx, cy, cz, cstart, cull2, sub, stride, walk);
+  walk_rows<DIM, R, PER, LPT, WIDE>(kp, cbase, pa, cx, cy, cz, cstart, cull2, sub, stride, walk);
   return acc;
 }
 
@@ -165,7 +165,7 @@ __device__ inline float shift_cull2(const KParams& kp, const uint32_t* __restric
 
 // C_a of one target (local key lk, cell keys offset by cbase) in every lane of
 // its LPT; lanes without a target (`live` false) take part in the sums over lanes.
-template <int DIM, int R, bool PER, int LPT>
+template <int DIM, int R, bool PER, int LPT, bool WIDE>
 __device__ inline float conc_one(const KParams& kp, bool live, uint32_t cbase, int64_t i,
                                  const float4* __restrict__ pr,
                                  const uint32_t* __restrict__ key,
@@ -176,8 +176,8 @@ __device__ inline float conc_one(const KParams& kp, bool live, uint32_t cbase, i
     const float4 pa = pr[i];
     int cx, cy, cz;
     target_cell(kp, key[i] - cbase, cx, cy, cz);
-    acc = shift_walk<DIM, R, PER, false, LPT>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
-                                              nullptr, 0.f, sub, lanes);
+    acc = shift_walk<DIM, R, PER, false, LPT, WIDE>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
+                                                    nullptr, 0.f, sub, lanes);
   }
   return conc_scale(kp) * lanes_sum(acc.s[0], lanes);
 }
@@ -186,7 +186,7 @@ __device__ inline float conc_one(const KParams& kp, bool live, uint32_t cbase, i
 // (Eq. 40-41, 53) for one fluid target i, with the tangential projection
 // below the surface threshold (Eq. 54, a_n = 0); dr_a is added to the
 // positions (and written to `shift` when given) by lane 0 of the target's LPT.
-template <int DIM, int R, bool PER, int LPT>
+template <int DIM, int R, bool PER, int LPT, bool WIDE>
 __device__ inline void shift_one(const KParams& kp, bool live, uint32_t cbase, int64_t n,
                                  int64_t i, const float4* __restrict__ pr,
                                  const float4* __restrict__ vp,
@@ -202,8 +202,8 @@ __device__ inline void shift_one(const KParams& kp, bool live, uint32_t cbase, i
     const float4 pa = pr[i];
     int cx, cy, cz;
     target_cell(kp, key[i] - cbase, cx, cy, cz);
-    acc = shift_walk<DIM, R, PER, true, LPT>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
-                                             conc, ca, sub, lanes);
+    acc = shift_walk<DIM, R, PER, true, LPT, WIDE>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
+                                                   conc, ca, sub, lanes);
   }
   const float kfab = kp.kfab_mf_f;
   const float g0 = kfab * lanes_sum(acc.s[0], lanes), g1 = kfab * lanes_sum(acc.s[1], lanes),
@@ -232,7 +232,7 @@ __device__ inline void shift_one(const KParams& kp, bool live, uint32_t cbase, i
   }
 }
 
-template <int DIM, int R, bool PER, int LPT>
+template <int DIM, int R, bool PER, int LPT, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_shift_conc(KParams kp, int64_t n,
                                                        const float4* __restrict__ pr,
                                                        const uint32_t* __restrict__ key,
@@ -245,11 +245,12 @@ __global__ __launch_bounds__(kBlock) void k_shift_conc(KParams kp, int64_t n,
   const int64_t i = shift_lane<LPT>(hdr, sub, lanes);
   const float cull2 = shift_cull2<R>(kp, disp, &hdr->err);
   const bool live = i < n && !is_excluded(type[i]);
-  const float c = conc_one<DIM, R, PER, LPT>(kp, live, 0u, i, pr, key, cstart, cull2, sub, lanes);
+  const float c =
+      conc_one<DIM, R, PER, LPT, WIDE>(kp, live, 0u, i, pr, key, cstart, cull2, sub, lanes);
   if (i < n && sub == 0) conc[i] = live ? c : 0.f;
 }
 
-template <int DIM, int R, bool PER, int LPT>
+template <int DIM, int R, bool PER, int LPT, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_shift_apply(
     KParams kp, int64_t n, const float4* __restrict__ pr, const float4* __restrict__ vp,
     const uint32_t* __restrict__ key, const uint32_t* __restrict__ cstart,
@@ -263,8 +264,8 @@ __global__ __launch_bounds__(kBlock) void k_shift_apply(
   const bool live = i < n && is_fluid(ty) && !is_excluded(ty);
   if (i < n && !live && shift && sub == 0)
     for (int d = 0; d < DIM; ++d) shift[d * n + i] = 0.f;
-  shift_one<DIM, R, PER, LPT>(kp, live, 0u, n, i, pr, vp, key, cstart, conc, dtp, cull2, pos,
-                              shift, sub, lanes);
+  shift_one<DIM, R, PER, LPT, WIDE>(kp, live, 0u, n, i, pr, vp, key, cstart, conc, dtp, cull2,
+                                    pos, shift, sub, lanes);
 }
 
 // ------------------------------------------------------------- batches --
@@ -297,7 +298,7 @@ __device__ inline float batch_shift_cull2(const KParams& kp, const uint32_t* __r
   return rc * rc;
 }
 
-template <int R, bool APPLY, bool PER>
+template <int R, bool APPLY, bool PER, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_batch_shift(
     const SlotEntry* __restrict__ tab, int ns, int64_t n, const float4* __restrict__ pr,
     const float4* __restrict__ vp, const uint32_t* __restrict__ key,
@@ -327,14 +328,14 @@ __global__ __launch_bounds__(kBlock) void k_batch_shift(
     const uint8_t t = type[i];
     if (!APPLY) {
       const bool live = !is_excluded(t);
-      const float c = conc_one<3, R, PER, 1>(kp, live, cbase, i, pr, key, cstart, cull2, 0, 1);
+      const float c = conc_one<3, R, PER, 1, WIDE>(kp, live, cbase, i, pr, key, cstart, cull2, 0, 1);
       conc[i] = live ? c : 0.f;
     } else {
       const bool live = is_fluid(t) && !is_excluded(t);
       if (!live && shift)
         for (int d = 0; d < 3; ++d) shift[d * n + i] = 0.f;
-      shift_one<3, R, PER, 1>(kp, live, cbase, n, i, pr, vp, key, cstart, conc, &dt[rs], cull2,
-                              pos, shift, 0, 1);
+      shift_one<3, R, PER, 1, WIDE>(kp, live, cbase, n, i, pr, vp, key, cstart, conc, &dt[rs],
+                                    cull2, pos, shift, 0, 1);
     }
   }
 }
@@ -360,25 +361,30 @@ hipError_t launch_shifting(const KParams& kp, int64_t n, const sph_state& s, con
   const uint32_t* disp = ws_ptr<uint32_t>(ws, L.disp);
   WsHeader* hdr = ws_ptr<WsHeader>(ws, L.err);
   const bool per = kp.periodic != 0;
-  const int lanes = shift_lanes(kp.dim, n);
+  // a large case or grid takes the walk with 64-bit offsets, one lane per target
+  // (a large grid may hold few particles: they need no speed)
+  const bool wide = !walk_fits_32(n, kp.ncell_total);
+  const int lanes = wide ? 1 : shift_lanes(kp.dim, n);
   // reused cells: one more cell of reach, cut widened by the displacement
   const int reach = kp.cell_div + (reuse ? 1 : 0);
-#define SPH_SHIFT(D, RR, PE, LP)                                                              \
+#define SPH_SHIFT(D, RR, PE, LP, WI)                                                          \
   do {                                                                                        \
     const dim3 grid(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u);                 \
     if (!given)                                                                               \
-      hipLaunchKernelGGL((k_shift_conc<D, RR, PE, LP>), grid, dim3(kBlock), 0, st, kp, n, pr, \
-                         key, cell_start, s.type, c, disp, hdr);                              \
-    hipLaunchKernelGGL((k_shift_apply<D, RR, PE, LP>), grid, dim3(kBlock), 0, st, kp, n,      \
+      hipLaunchKernelGGL((k_shift_conc<D, RR, PE, LP, WI>), grid, dim3(kBlock), 0, st, kp, n, \
+                         pr, key, cell_start, s.type, c, disp, hdr);                          \
+    hipLaunchKernelGGL((k_shift_apply<D, RR, PE, LP, WI>), grid, dim3(kBlock), 0, st, kp, n,  \
                        pr, vp, key, cell_start, s.type, c, dt, s.pos, shift, disp, hdr);      \
   } while (0)
-#define SPH_SHIFT_L2(RR, PE)                 \
-  if (lanes == 4) SPH_SHIFT(2, RR, PE, 4);   \
-  else SPH_SHIFT(2, RR, PE, 1)
-#define SPH_SHIFT_L3(RR, PE)                     \
-  if (lanes == 16) SPH_SHIFT(3, RR, PE, 16);     \
-  else if (lanes == 4) SPH_SHIFT(3, RR, PE, 4);  \
-  else SPH_SHIFT(3, RR, PE, 1)
+#define SPH_SHIFT_L2(RR, PE)                      \
+  if (lanes == 4) SPH_SHIFT(2, RR, PE, 4, false); \
+  else if (wide) SPH_SHIFT(2, RR, PE, 1, true);   \
+  else SPH_SHIFT(2, RR, PE, 1, false)
+#define SPH_SHIFT_L3(RR, PE)                           \
+  if (lanes == 16) SPH_SHIFT(3, RR, PE, 16, false);    \
+  else if (lanes == 4) SPH_SHIFT(3, RR, PE, 4, false); \
+  else if (wide) SPH_SHIFT(3, RR, PE, 1, true);        \
+  else SPH_SHIFT(3, RR, PE, 1, false)
 #define SPH_SHIFT_R(D)                                                                  \
   if (reach == 1) { if (per) { SPH_SHIFT_L##D(1, true); } else { SPH_SHIFT_L##D(1, false); } }      \
   else if (reach == 2) { if (per) { SPH_SHIFT_L##D(2, true); } else { SPH_SHIFT_L##D(2, false); } } \
@@ -412,21 +418,20 @@ hipError_t launch_batch_shifting(const BatchDesc& B, const sph_state& s, const u
   // reused cells: one more cell of reach, cut widened by each slot's record
   const int reach = B.cell_div + (reuse ? 1 : 0);
   const bool per = (B.flags & SPH_BATCH_PERIODIC) != 0;
-#define SPH_BSHIFT_P(RR, PE)                                                                    \
+  const bool wide = !walk_fits_32(n, (uint64_t)B.key_cells);
+#define SPH_BSHIFT_P(RR, PE, WI)                                                                \
   do {                                                                                          \
-    hipLaunchKernelGGL((k_batch_shift<RR, false, PE>), dim3(grid), dim3(kBlock), 0, st, tab,    \
+    hipLaunchKernelGGL((k_batch_shift<RR, false, PE, WI>), dim3(grid), dim3(kBlock), 0, st, tab, \
                        B.n_slots, n, pr, vp, key, cell_start, s.type, c, dt, s.pos, shift, disp, \
                        err, serr);                                                              \
-    hipLaunchKernelGGL((k_batch_shift<RR, true, PE>), dim3(grid), dim3(kBlock), 0, st, tab,     \
+    hipLaunchKernelGGL((k_batch_shift<RR, true, PE, WI>), dim3(grid), dim3(kBlock), 0, st, tab, \
                        B.n_slots, n, pr, vp, key, cell_start, s.type, c, dt, s.pos, shift, disp, \
                        err, serr);                                                              \
   } while (0)
-#define SPH_BSHIFT(RR)             \
-  do {                             \
-    if (per)                       \
-      SPH_BSHIFT_P(RR, true);      \
-    else                           \
-      SPH_BSHIFT_P(RR, false);     \
+#define SPH_BSHIFT(RR)                                                          \
+  do {                                                                          \
+    if (wide) { if (per) SPH_BSHIFT_P(RR, true, true); else SPH_BSHIFT_P(RR, false, true); } \
+    else { if (per) SPH_BSHIFT_P(RR, true, false); else SPH_BSHIFT_P(RR, false, false); }    \
   } while (0)
   if (reach == 1) {
     SPH_BSHIFT(1);
