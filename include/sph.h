@@ -291,7 +291,7 @@ sph_status sph_bin_cells(const sph_params* p, int64_t n, const sph_state* in,
  * Arithmetic is FP32 on cell-relative FP32 positions (Section 5.1, precision
  * paragraph).  Per-block maxima of |ace| and visc over fluid targets and the
  * interaction count go to the workspace for sph_reduce_dt.  n must be below
- * 2^28 and the grid below 2^30 cells (the walk addresses the view and the
+ * 2^28 - 4 and the grid below 2^30 cells (the walk addresses the view and the
  * cell ranges with 32-bit byte offsets), else SPH_E_ARG. */
 sph_status sph_interact(const sph_params* p, int64_t n, const sph_state* s,
                         const uint32_t* key, const uint32_t* cell_start,
@@ -337,8 +337,8 @@ sph_status sph_interact_noalloc(const sph_params* p, int64_t n, const sph_state*
  * same order); it only runs the wavefront's lanes through their own lists
  * instead of through common cell steps.  Default formulation only (Wendland
  * kernel, artificial viscosity, ddt 0 or 1, DBC walls, no floating bodies or
- * periodic components), FP32 state (no vel64/rho64) and n below 2^28; else
- * SPH_E_ARG.
+ * periodic components), FP32 state (no vel64/rho64) and sizes as for
+ * sph_interact; else SPH_E_ARG.
  *
  * The list is a caller-owned DEVICE buffer of sph_list_bytes(p, n) bytes (or
  * less: a smaller buffer holds fewer chunks per target, and targets whose

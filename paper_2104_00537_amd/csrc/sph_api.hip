@@ -237,7 +237,7 @@ sph_status sph_bin_cells(const sph_params* p, int64_t n, const sph_state* in, sp
 // byte offsets.
 static bool walk_size_ok(const sph_params* p, int64_t n) {
   const uint64_t cells = (uint64_t)p->ncell[0] * p->ncell[1] * p->ncell[2];
-  return n < ((int64_t)1 << 28) && cells < ((uint64_t)1 << 30);
+  return walk_fits_32(n, cells);
 }
 
 sph_status sph_interact(const sph_params* p, int64_t n, const sph_state* s, const uint32_t* key,

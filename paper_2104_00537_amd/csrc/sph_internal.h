@@ -162,8 +162,9 @@ constexpr int64_t kBatchLanesMaxN = 131072;
 
 // Whether the walk over the rows of a case of n particles on a grid of `cells`
 // cells can take 32-bit byte offsets: 16 bytes per particle in the views, with
-// room for the group of 4 that a range's end is tested with, and 4 per entry of
-// the cell ranges (`cells` + 1 of them).
+// room for the group of 4 that a range's end is tested with (o + 64 <= o1 wraps
+// for o = 16 (2^28 - 4), and the walk would not end), and 4 per entry of the cell
+// ranges (`cells` + 1 of them).
 inline bool walk_fits_32(int64_t n, uint64_t cells) {
   return n < ((int64_t)1 << 28) - 4 && cells < ((uint64_t)1 << 30);
 }

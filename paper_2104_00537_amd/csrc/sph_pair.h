@@ -270,8 +270,8 @@ __device__ __forceinline__ void load_group(const float4* __restrict__ pr, O o,
 
 // One group of NU (4, 2 or 1) consecutive candidates j..j+NU-1 of a row for
 // one target lane, all before the row's end j1 (o = 16 j and o1 = 16 j1 are
-// byte offsets into the views: 32 bits, which the calls' limit of n < 2^28
-// keeps exact): the candidate positions are loaded together, tested, then the
+// byte offsets into the views: 32 bits, exact for the sizes of walk_fits_32, as
+// is o + 64): the candidate positions are loaded together, tested, then the
 // velocities of the hits are loaded together and their pair terms
 // accumulated.  Along x the views hold fixed-point offsets (units of
 // kFrameCells*cs / 2^32, periodic over kFrameCells cells): the 32-bit

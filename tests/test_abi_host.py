@@ -455,3 +455,35 @@ def test_shifting_validates_without_device(S):
         assert shifting(P) == S.SPH_E_ARG
         assert lib.sph_interact(C.byref(P), 1000, C.byref(st), d, d, d, d, None, None, 0, d,
                                 need, None) == S.SPH_E_ARG
+
+
+def test_walk_sizes_end_where_offsets_would_wrap(S):
+    """The walk tests a range of candidates with a 32-bit byte offset 64 past
+    its own, which wraps from 2^28 - 4 particles on: such sizes are refused, the
+    ones below are not (they fail here on the workspace alone)."""
+    from paper_2104_00537_amd import cases
+    import dataclasses
+    cp = cases.dam_break_2d(dp=0.05).params
+    P = S.make_params(dataclasses.replace(cp, shift_coef=2.0))
+    lib = S.lib
+    d = C.c_void_p(16)
+    st = S.SphState(16, 16, 16, 16, 16, None)
+    reuse = S.SPH_INTERACT_REUSE_CELLS
+
+    def calls(n):
+        return (lib.sph_interact(C.byref(P), n, C.byref(st), d, d, d, d, None, None, 0, d, 0,
+                                 None),
+                lib.sph_interact_conc(C.byref(P), n, C.byref(st), d, d, d, d, None, reuse, d, 0,
+                                      None),
+                lib.sph_build_list(C.byref(P), n, C.byref(st), d, d, 0.0, 0, d, 1 << 40, d, 0,
+                                   None),
+                lib.sph_interact_list(C.byref(P), n, C.byref(st), d, d, d, 1 << 40, d, d, None,
+                                      None, 0, d, 0, None))
+
+    assert set(calls(2 ** 28 - 5)) == {S.SPH_E_WORKSPACE}
+    for n in (2 ** 28 - 4, 2 ** 28 - 1, 2 ** 28):
+        assert set(calls(n)) == {S.SPH_E_ARG}
+    assert S.sph_list_bytes(P, 2 ** 28 - 4) == 0 < S.sph_list_bytes(P, 2 ** 28 - 5)
+    # (shifting takes 64-bit offsets there)
+    assert lib.sph_shifting(C.byref(P), 2 ** 28, C.byref(st), d, d, d, None, None, 0, d, 0,
+                            None) == S.SPH_E_WORKSPACE
