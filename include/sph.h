@@ -431,7 +431,8 @@ sph_status sph_symplectic_step(const sph_params* p, int64_t n, int32_t phase,
  *     that dt, and sph_refresh_view of its result (key of the last binning);
  *   phase 1: *dt_half and interactions as by sph_reduce_dt (the time step of
  *     the second pass, which no update uses), and the corrector with *dt (key
- *     is not used).
+ *     is not used).  dt_half may be dt, which then takes the second pass's time
+ *     step before the corrector reads it, as with the separate calls.
  * Not for an all-FP64 state. */
 sph_status sph_symplectic_update(const sph_params* p, int64_t n, int32_t phase, double* dt,
                                  double* dt_half, uint64_t* interactions, double* t,

@@ -266,7 +266,9 @@ hipError_t launch_update(const KParams& kp, int64_t n, int phase, double* dt, do
   WsHeader* hdr = ws_ptr<WsHeader>(ws, L.err);
   uint32_t* disp = ws_ptr<uint32_t>(ws, L.disp);
   const BlockRed* red = ws_ptr<BlockRed>(ws, L.red);
-  if (n == 0) {
+  // (one buffer for both time steps: the corrector's blocks would read it while
+  // its first block writes it)
+  if (n == 0 || (phase == 1 && dt_half == dt)) {
     hipError_t e = launch_reduce_dt(kp, n, phase == 0 ? dt : dt_half, interactions, nullptr, ws, st);
     return e != hipSuccess ? e : launch_symplectic(kp, n, phase, dt, t, saved, s, ace, arho, ws, st);
   }

@@ -108,3 +108,35 @@ def test_one_call_matches_the_separate_calls(kind, n):
             scale = np.abs(a[ok].astype(np.float64)).max()
             err = np.abs(a[ok].astype(np.float64) - b[ok].astype(np.float64)).max()
             assert err <= tol * scale, (kind, tol, err, scale)
+
+
+def test_one_buffer_for_both_time_steps():
+    """dt_half = dt: the second pass's time step is written before the corrector
+    reads it, as in the separate calls; every result equals theirs."""
+    c = _case("fixed")
+    P, n, dim = S.make_params(c.params), c.n, c.params.dim
+    out = []
+    for fused in (False, True):
+        src, b = S.DeviceState.from_case(c, DEV), S.DeviceState.empty(dim, n, DEV)
+        saved = S.DeviceState.empty(dim, n, DEV)
+        key, perm = (torch.empty(n, dtype=torch.int32, device=DEV) for _ in range(2))
+        start = torch.empty(c.params.ncell_total() + 1, dtype=torch.int32, device=DEV)
+        ws = torch.zeros(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+        ace, arho = torch.zeros((dim, n), device=DEV), torch.zeros(n, device=DEV)
+        dt, t = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+        inter = torch.zeros(2, dtype=torch.int64, device=DEV)
+        S.sph_bin_cells(P, n, src, b, key, perm, start, ws)
+        S.sph_interact(P, n, b, key, start, ace, arho, ws)
+        S.sph_reduce_dt(P, n, dt, ws)
+        first = dt.item()
+        S.sph_symplectic_step(P, n, 0, dt, t, saved, b, ace, arho, ws)
+        S.sph_refresh_view(P, n, b, key, ws)
+        S.sph_interact(P, n, b, key, start, ace, arho, ws, flags=S.SPH_INTERACT_REUSE_CELLS)
+        if fused:
+            S.sph_symplectic_update(P, n, 1, dt, dt, inter, t, saved, b, ace, arho, key, ws)
+        else:
+            S.sph_reduce_dt(P, n, dt, ws, interactions=inter)
+            S.sph_symplectic_step(P, n, 1, dt, t, saved, b, ace, arho, ws)
+        assert dt.item() != first and t.item() == dt.item()
+        out.append((dt.clone(), t.clone(), inter, b.pos, b.vel, b.rho, b.type))
+    assert all(torch.equal(x, y) for x, y in zip(*out))
