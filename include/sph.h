@@ -426,7 +426,9 @@ sph_status sph_symplectic_step(const sph_params* p, int64_t n, int32_t phase,
                                void* stream);
 
 /* sph_reduce_dt and a phase of sph_symplectic_step in one call, with the same
- * results in fewer kernels (the step of a case without floating bodies):
+ * results in fewer kernels (the step of a case without floating bodies: phase 0
+ * with p->floating is SPH_E_ARG, as sph_floating_step moves the bodies' particles
+ * after the predictor and the view is refreshed after that):
  *   phase 0: *dt and interactions as by sph_reduce_dt, the predictor with
  *     that dt, and sph_refresh_view of its result (key of the last binning);
  *   phase 1: *dt_half and interactions as by sph_reduce_dt (the time step of

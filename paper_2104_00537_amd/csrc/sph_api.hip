@@ -377,6 +377,8 @@ sph_status sph_symplectic_update(const sph_params* p, int64_t n, int32_t phase, 
                                  size_t ws_bytes, void* stream) {
   if (!params_ok(p) || !n_ok(n) || !dt || !t || !ws) return SPH_E_ARG;
   if ((phase != 0 && phase != 1) || (phase == 1 && !dt_half)) return SPH_E_ARG;
+  // (floating particles move after the predictor: the view cannot be written yet)
+  if (phase == 0 && p->floating != 0) return SPH_E_ARG;
   if (n > 0 && (!state_ok(s, true) || !state_ok(saved, false) || !ace || !arho || f64_state(s) ||
                 (phase == 0 && !key)))
     return SPH_E_ARG;

@@ -242,7 +242,7 @@ class Simulation:
                  self.arho, self.ws, flags=self.flags, stream=stream)
         # dt, update and refresh in one call, unless each is timed by itself or
         # the floating bodies' step comes between them
-        fused = timing is None and self.bodies is None
+        fused = timing is None and self.bodies is None and not self.params.floating
         if fused:
             S.sph_symplectic_update(P, n, 0, self.dt, self.dt_half, self.interactions, self.t, s0,
                                     b, self.ace, self.arho, self.key, self.ws, stream=stream)

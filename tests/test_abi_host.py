@@ -487,3 +487,22 @@ def test_walk_sizes_end_where_offsets_would_wrap(S):
     # (shifting takes 64-bit offsets there)
     assert lib.sph_shifting(C.byref(P), 2 ** 28, C.byref(st), d, d, d, None, None, 0, d, 0,
                             None) == S.SPH_E_WORKSPACE
+
+
+def test_one_call_update_refuses_floating_bodies_in_the_predictor(S):
+    """Phase 0 writes the view, which sph_floating_step would leave behind; the
+    corrector writes none (the call fails here on the workspace alone)."""
+    from paper_2104_00537_amd import cases
+    P = S.make_params(cases.floating_box(2, dp=0.04).params)
+    d = C.c_void_p(16)
+    st = S.SphState(16, 16, 16, 16, 16, None)
+
+    def update(p, phase):
+        return S.lib.sph_symplectic_update(C.byref(p), 1000, phase, d, d, None, d, C.byref(st),
+                                           C.byref(st), d, d, d, d, 0, None)
+
+    assert P.floating == 1
+    assert update(P, 0) == S.SPH_E_ARG
+    assert update(P, 1) == S.SPH_E_WORKSPACE
+    P.floating = 0
+    assert update(P, 0) == S.SPH_E_WORKSPACE

@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     from paper_2104_00537_amd import sph as S
+    from paper_2104_00537_amd.runner import Simulation
 
 DEV = "cuda:0"
 
@@ -139,4 +140,20 @@ def test_one_buffer_for_both_time_steps():
             S.sph_symplectic_step(P, n, 1, dt, t, saved, b, ace, arho, ws)
         assert dt.item() != first and t.item() == dt.item()
         out.append((dt.clone(), t.clone(), inter, b.pos, b.vel, b.rho, b.type))
+    assert all(torch.equal(x, y) for x, y in zip(*out))
+
+
+def test_step_of_a_floating_case_without_bodies():
+    """floating = 1 and an empty body list: the step takes the separate calls,
+    timed or not, with the same results."""
+    out = []
+    for timing in (None, {}):
+        c = dataclasses.replace(cases.floating_box(2, dp=0.04), bodies=None)
+        c.vel[:, c.type == cases.FLUID] = np.float32(0.1)
+        sim = Simulation(c, DEV)
+        assert sim.reuse_cells and sim.params.floating == 1
+        for _ in range(3):
+            sim.step(timing=timing)
+        assert sim.error() == 0
+        out.append((sim.state.pos, sim.state.vel, sim.state.rho, sim.t))
     assert all(torch.equal(x, y) for x, y in zip(*out))
