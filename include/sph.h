@@ -503,8 +503,9 @@ sph_status sph_mdbc(const sph_params* p, int64_t n, sph_state* s, const uint32_t
  * flag): the search then reaches one cell further and widens its cut by the
  * recorded displacement, as in sph_interact (SPH_ERR_MARGIN past half a
  * cell; not with modified DBC).  Other bits: SPH_E_ARG.  Small cases take
- * several lanes per particle, unless the interaction before took one
- * (SPH_INTERACT_ONE_LANE). */
+ * several lanes per particle, unless the last interaction on the workspace since
+ * the binning took one (SPH_INTERACT_ONE_LANE, a precision-study arm, a
+ * neighbour list, or a large case). */
 sph_status sph_shifting(const sph_params* p, int64_t n, sph_state* s, const uint32_t* key,
                         const uint32_t* cell_start, const double* dt, float* conc,
                         float* shift, uint32_t flags, void* ws, size_t ws_bytes, void* stream);

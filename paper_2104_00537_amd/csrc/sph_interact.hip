@@ -50,6 +50,7 @@ __global__ __launch_bounds__(kBlock) void k_interact_arm(
   const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   float fmag = 0.f, vmax_out = 0.f;
   uint32_t cnt_out = 0, cnt_wall = 0, nfl = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) hdr->one_lane = 1u;
   if (i < n) {
     if (!is_excluded(type[i]) && (kp.boundary == 0 || is_fluid(type[i]))) {
       const float4 pa = pr[i], va = vp[i];

@@ -181,7 +181,10 @@ __global__ __launch_bounds__(kBlock) void k_interact_list(
     if (delta > 0.f) set_error(&hdr->err, SPH_ERR_MARGIN);
     if (stale) atomicAdd(&hdr->list_walks, 1u);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && stale) set_error(&hdr->err, SPH_ERR_LIST);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (stale) set_error(&hdr->err, SPH_ERR_LIST);
+    hdr->one_lane = 1u;
+  }
   if (i < n) {
     if (!is_excluded(type[i]) && (kp.boundary == 0 || is_fluid(type[i]))) {
       PairAcc acc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0u};

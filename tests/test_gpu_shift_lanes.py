@@ -111,3 +111,40 @@ def test_concentration_of_the_interaction(dim, shape, option):
         if lanes:
             assert torch.equal(a[2], b[2])
     assert S.sph_read_error(ws) == 0
+
+
+@pytest.mark.parametrize("kind", ["list", "arm"])
+def test_shifting_takes_one_lane_after_a_pass_that_did(kind):
+    """The neighbour-list pass and the precision arms always take one lane per
+    target: shifting after them gives the bits of shifting after
+    SPH_INTERACT_ONE_LANE, whatever pass ran before them."""
+    c = _case(3, (15, 14, 9), "default")
+    n, P0 = c.n, S.make_params(c.params)
+    c.params.shift_coef, c.params.shift_fs = 2.0, 0.9
+    P = S.make_params(c.params)
+    src, dst = S.DeviceState.from_case(c, DEV), S.DeviceState.empty(3, n, DEV)
+    key, perm = (torch.empty(n, dtype=torch.int32, device=DEV) for _ in range(2))
+    start = torch.empty(c.params.ncell_total() + 1, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+    lst = torch.empty(S.sph_list_bytes(P0, n), dtype=torch.uint8, device=DEV)
+    dt = torch.full((1,), 1e-4, dtype=torch.float64, device=DEV)
+    ace, arho = torch.empty((3, n), device=DEV), torch.empty(n, device=DEV)
+    S.sph_bin_cells(P, n, src, dst, key, perm, start, ws)
+    S.sph_build_list(P0, n, dst, key, start, 0.01 * c.params.h, lst, ws)
+    out = []
+    for one in (True, False):
+        if one:
+            S.sph_interact(P, n, dst, key, start, ace, arho, ws, flags=S.SPH_INTERACT_ONE_LANE)
+        else:
+            S.sph_interact(P, n, dst, key, start, ace, arho, ws)
+            if kind == "list":
+                S.sph_interact_list(P0, n, dst, key, start, lst, ace, arho, ws)
+            else:
+                S.sph_interact(P, n, dst, key, start, ace, arho, ws, flags=S.SPH_INTERACT_ABS_F32)
+        keep = dst.pos.clone()
+        conc, shift = torch.empty(n, device=DEV), torch.empty((3, n), device=DEV)
+        S.sph_shifting(P, n, dst, key, start, dt, ws, conc=conc, shift=shift)
+        dst.pos.copy_(keep)
+        out.append((conc, shift))
+    assert S.sph_read_error(ws) == 0
+    assert all(torch.equal(x, y) for x, y in zip(*out))
