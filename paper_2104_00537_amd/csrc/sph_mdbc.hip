@@ -168,12 +168,13 @@ __global__ __launch_bounds__(kBlock, 4) void k_mdbc(KParams kp, int64_t n, sph_s
                                                  float4* __restrict__ pr,
                                                  float4* __restrict__ vp,
                                                  const uint32_t* __restrict__ list,
-                                                 const WsHeader* __restrict__ hdr) {
+                                                 const WsHeader* __restrict__ hdr, int64_t w0) {
   constexpr int M = DIM + 1;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int sub = (int)(t % kMdbcLanes);
-  if (t / kMdbcLanes >= (int64_t)hdr->nwall) return;  // (all lanes of a wall together)
-  const int64_t i = list[t / kMdbcLanes];
+  const int64_t wall = w0 + t / kMdbcLanes;
+  if (wall >= (int64_t)hdr->nwall) return;  // (all lanes of a wall together)
+  const int64_t i = list[wall];
   double g[3] = {0.0, 0.0, 0.0}, rb[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
@@ -359,19 +360,25 @@ hipError_t launch_mdbc(const KParams& kp, int64_t n, const sph_state& s, const u
   // the work list lives in the sort's key buffer, free once the cells are
   // binned (sph_bin_cells must not run between this and the next launch)
   uint32_t* list = ws_ptr<uint32_t>(ws, L.keyA);
-  // (room for every particle being a wall; blocks past the list leave at once)
-  const unsigned grid = (unsigned)((n * kMdbcLanes + kBlock - 1) / kBlock);
   const int64_t chunk = kBlock * kListRounds;
   hipLaunchKernelGGL(k_zero_wall_count, dim3(1), dim3(64), 0, st, hdr);
   hipLaunchKernelGGL(k_wall_list, dim3((unsigned)((n + chunk - 1) / chunk)), dim3(kBlock), 0, st,
                      n, s.type, list, hdr);
+  // room for every particle being a wall (blocks past the list leave at once),
+  // kLaunchWalls walls a launch: a launch has fewer than 2^32 threads
+  constexpr int64_t kLaunchWalls = (int64_t)1 << 29;
+  static_assert(kLaunchWalls * kMdbcLanes < ((int64_t)1 << 32), "threads of a launch");
 #define SPH_MDBC(D, RR)                                                                    \
   hipLaunchKernelGGL((k_mdbc<D, RR>), dim3(grid), dim3(kBlock), 0, st, kp, n, s, cell_start, \
-                     pr, vp, list, hdr)
-  if (kp.dim == 2) {
-    if (kp.cell_div == 1) SPH_MDBC(2, 1); else SPH_MDBC(2, 2);
-  } else {
-    if (kp.cell_div == 1) SPH_MDBC(3, 1); else SPH_MDBC(3, 2);
+                     pr, vp, list, hdr, w0)
+  for (int64_t w0 = 0; w0 < n; w0 += kLaunchWalls) {
+    const int64_t walls = n - w0 < kLaunchWalls ? n - w0 : kLaunchWalls;
+    const unsigned grid = (unsigned)((walls * kMdbcLanes + kBlock - 1) / kBlock);
+    if (kp.dim == 2) {
+      if (kp.cell_div == 1) SPH_MDBC(2, 1); else SPH_MDBC(2, 2);
+    } else {
+      if (kp.cell_div == 1) SPH_MDBC(3, 1); else SPH_MDBC(3, 2);
+    }
   }
 #undef SPH_MDBC
   return hipGetLastError();

@@ -101,3 +101,38 @@ def test_mdbc_dam_break_2d_front_against_oracle():
     _say(f"  mDBC front after 300 steps: gpu {fg:.5f} oracle {fo:.5f}")
     assert abs(fg - fo) < 1e-3 * 1.6
     assert st["t"] == pytest.approx(out["t"], rel=1e-4)
+
+
+def test_wall_pass_of_more_than_2_30_particles():
+    """The wall pass launches several lanes per wall, and a launch holds fewer
+    than 2^32 threads: a small case followed by excluded particles up to 2^30 and
+    some gives the small case's walls, bit for bit."""
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 140 * 2 ** 30:
+        pytest.skip("needs 140 GiB of device memory")
+    c = cases.dam_break_2d(dp=0.02, cell_div=2, x_sub=4)
+    c.params = dataclasses.replace(c.params, boundary=1)
+    c.vel[:] = np.random.default_rng(7).uniform(-0.3, 0.3, c.vel.shape).astype(np.float32)
+    m, n, P = c.n, 2 ** 30 + 64, S.make_params(c.params)
+    print("wall pass of", n, "particles", flush=True)
+    src = S.DeviceState.from_case(c, DEV, with_normal=True)
+    small = S.DeviceState.empty(2, m, DEV, with_normal=True)
+    key, perm = (torch.empty(m, dtype=torch.int32, device=DEV) for _ in range(2))
+    start = torch.empty(c.params.ncell_total() + 1, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(S.sph_workspace_bytes(P, m), dtype=torch.uint8, device=DEV)
+    S.sph_bin_cells(P, m, src, small, key, perm, start, ws)
+    big = S.DeviceState.empty(2, n, DEV, with_id=False, with_normal=True)
+    big.type.fill_(cases.EXCLUDED)
+    for a, b in ((big.pos, small.pos), (big.vel, small.vel), (big.rho, small.rho),
+                 (big.type, small.type), (big.normal, small.normal)):
+        a[..., :m] = b
+    bkey = torch.empty(n, dtype=torch.int32, device=DEV)
+    bkey[:m] = key
+    bws = torch.empty(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+    bws[:4096].zero_()
+    S.sph_mdbc(P, m, small, key, start, ws)
+    S.sph_refresh_view(P, n, big, bkey, bws)
+    S.sph_mdbc(P, n, big, bkey, start, bws)
+    assert torch.equal(big.rho[:m], small.rho)
+    wall = small.type != 0
+    assert wall.any() and (small.rho[wall] != src.rho[perm.long()][wall]).any()
