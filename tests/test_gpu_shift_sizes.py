@@ -136,6 +136,7 @@ def test_shifting_of_more_than_2_28_particles():
     nx, nz = 16384, 16400
     n = nx * nz
     assert n > 2 ** 28
+    torch.cuda.empty_cache()
     if torch.cuda.mem_get_info()[0] < 80 * 2 ** 30:
         pytest.skip("needs 80 GiB of device memory")
     print("shifting of", n, "particles", flush=True)
