@@ -304,7 +304,7 @@ sph_status sph_interact(const sph_params* p, int64_t n, const sph_state* s,
  * hipMalloc.  sph_interact without a workspace: the regions the pass needs
  * besides its inputs and outputs (the interaction view, built here from s;
  * the per-block partial results; an error word) live in one device array of
- * the library, 70 MB (for SPH_NOALLOC_MAX_N particles), which each GPU the
+ * the library, 68 MB (for SPH_NOALLOC_MAX_N particles), which each GPU the
  * library runs on holds until the process ends.
  *   s, key, cell_start   as sph_bin_cells left them (s sorted; positions,
  *                        velocities, densities and types not changed since)

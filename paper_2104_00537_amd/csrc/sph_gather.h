@@ -170,7 +170,7 @@ k_interact_gather(
 //        185k: 25 / 27 / 33 / 41 / 69
 inline int lanes_per_target(int dim, int64_t n) {
   if (dim == 2) return n <= 32768 ? 4 : n <= 122880 ? 2 : 1;
-  return n <= 24576 ? 16 : n <= 65536 ? 8 : n <= 98304 ? 4 : n <= 327680 ? 2 : 1;
+  return n <= 24576 ? 16 : n <= 65536 ? 8 : n <= 98304 ? 4 : n <= kLanesMaxN ? 2 : 1;
 }
 
 template <int DIM>

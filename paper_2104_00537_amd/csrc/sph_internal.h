@@ -153,10 +153,11 @@ struct SlotMotion {
   double dt, dmove, vmove, pad;
 };
 
-// Most lanes that share one target particle in the interaction (see
-// lanes_per_target), and for a slot of a batch (SPH_BATCH_FOUR_LANES) with
-// the largest slot that gets them.
+// Most lanes that share one target particle in the interaction, the largest case
+// that gets more than one (see lanes_per_target), and for a slot of a batch
+// (SPH_BATCH_FOUR_LANES) with the largest slot that gets them.
 constexpr int kMaxLanes = 16;
+constexpr int64_t kLanesMaxN = 327680;
 constexpr int kBatchLanes = 4;
 constexpr int64_t kBatchLanesMaxN = 131072;
 
@@ -187,6 +188,13 @@ struct WsLayout {
   int64_t nblk_interact;
 };
 
+// Blocks of an interaction pass over n particles, whatever its lanes per target.
+constexpr int64_t interact_blocks(int64_t n) {
+  const int64_t one = (n + kBlock - 1) / kBlock;
+  const int64_t most = (n < kLanesMaxN ? n : kLanesMaxN) * kMaxLanes / kBlock + 1;
+  return one > most ? one : most;
+}
+
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 inline WsLayout ws_layout(int64_t n) {
@@ -206,8 +214,7 @@ inline WsLayout ws_layout(int64_t n) {
   // in groups of 4 with scalar loads that may run past the last particle
   L.view_pr = off; off = align_up(off + 16 * (nn + kViewPad));
   L.view_vp = off; off = align_up(off + 16 * (nn + kViewPad));
-  // (room for the blocks of kMaxLanes lanes per target)
-  L.red = off; off = align_up(off + sizeof(BlockRed) * (size_t)L.nblk_interact * kMaxLanes);
+  L.red = off; off = align_up(off + sizeof(BlockRed) * (size_t)interact_blocks(n));
   L.disp = off; off = align_up(off + sizeof(uint32_t) * kDispSlots);
   L.fpart = off;
   off = align_up(off + sizeof(double) * SPH_MAX_BODIES * kFloatParts * kFloatSums);

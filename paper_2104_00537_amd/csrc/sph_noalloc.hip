@@ -16,13 +16,13 @@ namespace sph {
 namespace {
 
 constexpr int64_t kNaMaxN = SPH_NOALLOC_MAX_N;
-constexpr int64_t kNaBlocks = (kNaMaxN + kBlock - 1) / kBlock;
+constexpr int64_t kNaBlocks = interact_blocks(kNaMaxN);
 constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // layout of the array (offsets in bytes)
 constexpr size_t kNaHdr = 0;
 constexpr size_t kNaDisp = align256(kNaHdr + sizeof(WsHeader));
 constexpr size_t kNaRed = align256(kNaDisp + sizeof(uint32_t) * kDispSlots);
-constexpr size_t kNaPr = align256(kNaRed + sizeof(BlockRed) * kNaBlocks * kMaxLanes);
+constexpr size_t kNaPr = align256(kNaRed + sizeof(BlockRed) * kNaBlocks);
 constexpr size_t kNaVp = align256(kNaPr + 16 * (size_t)(kNaMaxN + kViewPad));
 constexpr size_t kNaTotal = align256(kNaVp + 16 * (size_t)(kNaMaxN + kViewPad));
 

@@ -506,3 +506,16 @@ def test_one_call_update_refuses_floating_bodies_in_the_predictor(S):
     assert update(P, 1) == S.SPH_E_WORKSPACE
     P.floating = 0
     assert update(P, 0) == S.SPH_E_WORKSPACE
+
+
+def test_workspace_holds_one_partial_per_block_of_a_large_case(S):
+    """Only cases of up to a few hundred thousand particles take several lanes per
+    target, so the room for their blocks' partials does not grow with n: 48 bytes
+    of keys, members and views, 1/16 of a word of counts and 24/256 bytes of
+    partials per particle; and the size never falls."""
+    from paper_2104_00537_amd import cases
+    P = S.make_params(cases.dam_break_3d(dp=0.05).params)
+    per = (S.sph_workspace_bytes(P, 2 * 10 ** 7) - S.sph_workspace_bytes(P, 10 ** 7)) / 10 ** 7
+    assert 48.0 < per < 48.0 + 1 / 16 + 24 / 256 + 1e-3
+    sizes = [S.sph_workspace_bytes(P, n) for n in range(0, 6_000_000, 997)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
