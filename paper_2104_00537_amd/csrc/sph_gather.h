@@ -185,8 +185,13 @@ hipError_t launch_gather(const KParams& kp, int64_t n, const sph_state& s, const
   const bool gen = kp.kernel != 0 || kp.viscosity != 0 || kp.ddt == 2 || kp.floating != 0;
   const bool per = kp.periodic != 0;
   int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n);
-  // the diagnostic count and unequal masses come with one lane or four
-  if ((diag || !eqm) && lanes > 1) lanes = 4;
+  // the diagnostic count and unequal masses come with one lane or four, and lose
+  // with four sooner (us per pass, 1 / 4 lanes):
+  //   3-D, unequal masses   100k: 117 / 91    140k: 127 / 124, reused cells 129 / 142
+  //        count            100k: 236 / 224   140k: 277 / 299   304k: 417 / 598
+  //   2-D, unequal masses    54k: 17 / 15     105k: 21 / 23
+  //        count             54k: 25 / 22     105k: 30 / 36
+  if ((diag || !eqm) && lanes > 1) lanes = n <= (DIM == 2 ? 65536 : 131072) ? 4 : 1;
 #define SPH_LAUNCH(D, RR, G, PP, GG, PE, LP)                                                  \
   hipLaunchKernelGGL((k_interact_gather<D, RR, G, PP, GG, PE, LP>),                           \
                      dim3(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u),           \

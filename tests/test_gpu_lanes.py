@@ -80,3 +80,34 @@ def test_lanes_agree_with_one(dim, shape, lanes, option):
             S.sph_symplectic_step(P, n, 0, dt, t, saved, dst, single[0], single[1], ws)
             S.sph_refresh_view(P, n, dst, key, ws)
     assert S.sph_read_error(ws) == 0
+
+
+def _rates(P, n, dst, key, start, ws, flags):
+    dim = dst.pos.shape[0]
+    ace = torch.full((dim, n), float("nan"), device=DEV)
+    arho, visc = (torch.full((n,), float("nan"), device=DEV) for _ in range(2))
+    nbr = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    S.sph_interact(P, n, dst, key, start, ace, arho, ws, visc=visc, nbr=nbr, flags=flags)
+    return ace, arho, visc, nbr
+
+
+@pytest.mark.parametrize("dim,shape,option,diag", [
+    (3, (52, 48, 44), "unequal", False), (3, (52, 48, 44), "default", True),
+    (3, (60, 60, 50), "unequal", False), (3, (60, 60, 50), "options", True),
+    (2, (300, 220), "unequal", False), (2, (300, 220), "default", True)])
+def test_one_lane_where_four_are_slower(dim, shape, option, diag):
+    """Unequal masses and the diagnostic count come with four lanes or one; where
+    four are slower (from 131,072 particles in 3-D and 65,536 in 2-D on) the
+    default launch has the bits of one lane."""
+    c = _case(dim, shape, option)
+    n, P = c.n, S.make_params(c.params)
+    assert (131072 if dim == 3 else 65536) < n <= 327680
+    src, dst = S.DeviceState.from_case(c, DEV), S.DeviceState.empty(dim, n, DEV)
+    key, perm = (torch.empty(n, dtype=torch.int32, device=DEV) for _ in range(2))
+    start = torch.empty(c.params.ncell_total() + 1, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(S.sph_workspace_bytes(P, n), dtype=torch.uint8, device=DEV)
+    S.sph_bin_cells(P, n, src, dst, key, perm, start, ws)
+    flag = S.SPH_DIAG_COUNT_F64 if diag else 0
+    many = _rates(P, n, dst, key, start, ws, flag)
+    one = _rates(P, n, dst, key, start, ws, flag | S.SPH_INTERACT_ONE_LANE)
+    assert all(torch.equal(a, b) for a, b in zip(many, one))
