@@ -46,9 +46,15 @@ __device__ __forceinline__ void key_cell(const KParams& kp, uint32_t k, int& cx,
 //   3-D, 1.32M: 7 573 / 576, 8 (it spills) 591 / 593; 1.58M: 699 / 703, 723 / 723
 //   3-D periodic, 958k: 6 604 / 610, 7 574 / 579, 8 621 / 630
 //   3-D with options, 441k: 5 304 / 307, 6 266 / 268, 7 271 / 272
-// With several lanes per target the better number changes with the size (2 lanes:
-// 223k 124 at 6 and 128 at 7, 294k 180 and 167): left to the compiler.
-constexpr int gather_waves(int dim, bool plain, bool gen, int lpt) {
+// With several lanes per target the registers are left to the compiler, which
+// gives the 2 lanes of the default formulation in 3-D 6 wavefronts.  A case of more
+// wavefronts than that (HOLD, from kHoldMinN particles on) ends on a second round
+// of few of them and is faster held to 7, a smaller one slower (us per pass, 6 / 7:
+// filled box 192k 131 / 131, 221k 165 / 142; dam break 153k 96 / 97, on reused cells
+// 102 / 105).
+constexpr int64_t kHoldMinN = 6 * kSimds * 64 / 2;
+constexpr int gather_waves(int dim, bool plain, bool gen, int lpt, bool hold) {
+  if (hold) return 7;
   if (!plain || (dim == 2 && gen) || (dim == 3 && lpt > 1)) return 1;
   return dim == 2 ? 8 : gen ? 6 : 7;
 }
@@ -56,8 +62,9 @@ constexpr int gather_waves(int dim, bool plain, bool gen, int lpt) {
 // LPT lanes per target particle (sorted order): 1 is the production kernel of
 // large cases; more deal each target's rows to that many lanes, for cases too
 // small to fill the GPU (see lanes_per_target).
-template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT, bool CONC = false>
-__global__ __launch_bounds__(kBlock, gather_waves(DIM, EQM && !DIAG, GEN, LPT)) void
+template <int DIM, int R, bool DIAG, bool EQM, bool GEN, bool PER, int LPT, bool CONC = false,
+          bool HOLD = false>
+__global__ __launch_bounds__(kBlock, gather_waves(DIM, EQM && !DIAG, GEN, LPT, HOLD)) void
 k_interact_gather(
     KParams kp, int64_t n, const float4* __restrict__ pr, const float4* __restrict__ vp,
     const uint32_t* __restrict__ key, const uint32_t* __restrict__ cstart,
@@ -168,9 +175,17 @@ k_interact_gather(
 //        223k: 164 / 124 / 144 / 158 / 189  441k: 220 / 234 / 292 / 321 / 387
 //   2-D   14k: 17 / 12 / 9.7 / 9.6 / 10     54k: 18 / 14 / 15 / 16 / 24
 //        185k: 25 / 27 / 33 / 41 / 69
-inline int lanes_per_target(int dim, int64_t n) {
+// The last line of 3-D is that of a filled box, whose targets are nearly all fluid,
+// and of the pass on reused cells (1 / 2 lanes, held as above from 197k on; the dam
+// break, half of it walls, crosses at about 300k):
+//   filled box, reused cells   221k: 179 / 155   244k: 185 / 186   260k: 190 / 200
+//   open block, reused cells   229k: 175 / 164   252k: 189 / 201
+//   dam break, reused cells    216k: 165 / 135   273k: 162 / 157   315k: 183 / 195
+// With options (gen) two lanes have 5 wavefronts per SIMD and lose sooner: reused
+// cells, cubic spline 173k: 206 / 179   184k: 198 / 193   192k: 203 / 208.
+inline int lanes_per_target(int dim, int64_t n, bool gen) {
   if (dim == 2) return n <= 32768 ? 4 : n <= 122880 ? 2 : 1;
-  return n <= 24576 ? 16 : n <= 65536 ? 8 : n <= 98304 ? 4 : n <= kLanesMaxN ? 2 : 1;
+  return n <= 24576 ? 16 : n <= 65536 ? 8 : n <= 98304 ? 4 : n <= (gen ? 184320 : kLanesMaxN) ? 2 : 1;
 }
 
 template <int DIM>
@@ -184,7 +199,8 @@ hipError_t launch_gather(const KParams& kp, int64_t n, const sph_state& s, const
   const bool eqm = kp.mass_f == kp.mass_b;
   const bool gen = kp.kernel != 0 || kp.viscosity != 0 || kp.ddt == 2 || kp.floating != 0;
   const bool per = kp.periodic != 0;
-  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n);
+  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n, gen);
+  const bool hold = n > kHoldMinN;
   // the diagnostic count and unequal masses come with one lane or four, and lose
   // with four sooner (us per pass, 1 / 4 lanes):
   //   3-D, unequal masses   100k: 117 / 91    140k: 127 / 124, reused cells 129 / 142
@@ -192,8 +208,8 @@ hipError_t launch_gather(const KParams& kp, int64_t n, const sph_state& s, const
   //   2-D, unequal masses    54k: 17 / 15     105k: 21 / 23
   //        count             54k: 25 / 22     105k: 30 / 36
   if ((diag || !eqm) && lanes > 1) lanes = n <= (DIM == 2 ? 65536 : 131072) ? 4 : 1;
-#define SPH_LAUNCH(D, RR, G, PP, GG, PE, LP)                                                  \
-  hipLaunchKernelGGL((k_interact_gather<D, RR, G, PP, GG, PE, LP>),                           \
+#define SPH_LAUNCH(D, RR, G, PP, GG, PE, LP, HO)                                              \
+  hipLaunchKernelGGL((k_interact_gather<D, RR, G, PP, GG, PE, LP, false, HO>),                \
                      dim3(n > 0 ? (unsigned)((n * LP + kBlock - 1) / kBlock) : 1u),           \
                      dim3(kBlock), 0, st, kp, n, w.pr, w.vp, key, cell_start, s.type, s.pos, ace, \
                      arho, visc, nbr, w.red, w.hdr, w.disp, nullptr)
@@ -202,10 +218,10 @@ hipError_t launch_gather(const KParams& kp, int64_t n, const sph_state& s, const
 // default formulation need not pay (958k particles in a periodic channel:
 // 715 -> 608 us a pass; the same operations, the same results).
 #define SPH_LAUNCH_F(D, RR, G, PP, LP)                  \
-  if (per && gen) SPH_LAUNCH(D, RR, G, PP, true, true, LP); \
-  else if (per) SPH_LAUNCH(D, RR, G, PP, false, true, LP); \
-  else if (gen) SPH_LAUNCH(D, RR, G, PP, true, false, LP); \
-  else SPH_LAUNCH(D, RR, G, PP, false, false, LP)
+  if (per && gen) SPH_LAUNCH(D, RR, G, PP, true, true, LP, false); \
+  else if (per) SPH_LAUNCH(D, RR, G, PP, false, true, LP, false); \
+  else if (gen) SPH_LAUNCH(D, RR, G, PP, true, false, LP, false); \
+  else SPH_LAUNCH(D, RR, G, PP, false, false, LP, false)
 #define SPH_LAUNCH_1(D, RR, G, PP)                      \
   if (lanes == 1) { SPH_LAUNCH_F(D, RR, G, PP, 1); }    \
   else { SPH_LAUNCH_F(D, RR, G, PP, 4); }
@@ -215,7 +231,10 @@ hipError_t launch_gather(const KParams& kp, int64_t n, const sph_state& s, const
   else { SPH_LAUNCH_F(2, RR, false, true, 4); }
 #define SPH_LAUNCH_3(RR)                                         \
   if (lanes == 1) { SPH_LAUNCH_F(3, RR, false, true, 1); }       \
-  else if (lanes == 2) { SPH_LAUNCH_F(3, RR, false, true, 2); }  \
+  else if (lanes == 2 && hold && !gen) {                         \
+    if (per) SPH_LAUNCH(3, RR, false, true, false, true, 2, true); \
+    else SPH_LAUNCH(3, RR, false, true, false, false, 2, true);  \
+  } else if (lanes == 2) { SPH_LAUNCH_F(3, RR, false, true, 2); } \
   else if (lanes == 4) { SPH_LAUNCH_F(3, RR, false, true, 4); }  \
   else if (lanes == 8) { SPH_LAUNCH_F(3, RR, false, true, 8); }  \
   else { SPH_LAUNCH_F(3, RR, false, true, 16); }

@@ -14,25 +14,33 @@ hipError_t launch_interact_conc(const KParams& kp, int64_t n, const sph_state& s
                                 hipStream_t st) {
   const WsLayout L = ws_layout(n);
   float* c = conc ? conc : ws_ptr<float>(ws, L.keyA);
-  const int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n);
+  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n, false);
+  // C takes registers: 5 wavefronts of two lanes per target in a periodic channel,
+  // so that they are held to 7 sooner than without it, and one lane is faster as
+  // soon as 7 do not hold the case (us per pass, two lanes 5 / 7 wavefronts, one:
+  // channel 168k 179 / 195, 228; 194k 252 / 223, 243; filled box 173k 141 / 145, 175;
+  // 192k 149 / 151, 170; 238k - / 195, 182)
+  const bool hold = n > 184320;
+  if (lanes == 2 && kp.dim == 3 && n > 7 * kSimds * 64 / 2) lanes = 1;
   const bool per = kp.periodic != 0;
-#define SPH_CONC(D, RR, PE, LP)                                                                \
-  hipLaunchKernelGGL((k_interact_gather<D, RR, false, true, false, PE, LP, true>),             \
+#define SPH_CONC(D, RR, PE, LP, HO)                                                            \
+  hipLaunchKernelGGL((k_interact_gather<D, RR, false, true, false, PE, LP, true, HO>),         \
                      dim3((unsigned)((n * LP + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,    \
                      kp, n, ws_ptr<float4>(ws, L.view_pr), ws_ptr<float4>(ws, L.view_vp), key, \
                      cell_start, s.type, s.pos, ace, arho, nullptr, nullptr,                   \
                      ws_ptr<BlockRed>(ws, L.red), ws_ptr<WsHeader>(ws, L.err),                 \
                      ws_ptr<uint32_t>(ws, L.disp), c)
 #define SPH_CONC_L2(RR, PE)                  \
-  if (lanes == 1) SPH_CONC(2, RR, PE, 1);    \
-  else if (lanes == 2) SPH_CONC(2, RR, PE, 2); \
-  else SPH_CONC(2, RR, PE, 4)
-#define SPH_CONC_L3(RR, PE)                    \
-  if (lanes == 1) SPH_CONC(3, RR, PE, 1);      \
-  else if (lanes == 2) SPH_CONC(3, RR, PE, 2); \
-  else if (lanes == 4) SPH_CONC(3, RR, PE, 4); \
-  else if (lanes == 8) SPH_CONC(3, RR, PE, 8); \
-  else SPH_CONC(3, RR, PE, 16)
+  if (lanes == 1) SPH_CONC(2, RR, PE, 1, false);    \
+  else if (lanes == 2) SPH_CONC(2, RR, PE, 2, false); \
+  else SPH_CONC(2, RR, PE, 4, false)
+#define SPH_CONC_L3(RR, PE)                           \
+  if (lanes == 1) SPH_CONC(3, RR, PE, 1, false);      \
+  else if (lanes == 2 && hold) SPH_CONC(3, RR, PE, 2, true); \
+  else if (lanes == 2) SPH_CONC(3, RR, PE, 2, false); \
+  else if (lanes == 4) SPH_CONC(3, RR, PE, 4, false); \
+  else if (lanes == 8) SPH_CONC(3, RR, PE, 8, false); \
+  else SPH_CONC(3, RR, PE, 16, false)
 #define SPH_CONC_P(D, RR)                      \
   if (per) { SPH_CONC_L##D(RR, true); }        \
   else { SPH_CONC_L##D(RR, false); }

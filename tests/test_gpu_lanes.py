@@ -94,11 +94,13 @@ def _rates(P, n, dst, key, start, ws, flags):
 @pytest.mark.parametrize("dim,shape,option,diag", [
     (3, (52, 48, 44), "unequal", False), (3, (52, 48, 44), "default", True),
     (3, (60, 60, 50), "unequal", False), (3, (60, 60, 50), "options", True),
-    (2, (300, 220), "unequal", False), (2, (300, 220), "default", True)])
-def test_one_lane_where_four_are_slower(dim, shape, option, diag):
-    """Unequal masses and the diagnostic count come with four lanes or one; where
-    four are slower (from 131,072 particles in 3-D and 65,536 in 2-D on) the
-    default launch has the bits of one lane."""
+    (2, (300, 220), "unequal", False), (2, (300, 220), "default", True),
+    (3, (64, 60, 54), "default", False), (3, (60, 56, 46), "options", False)])
+def test_one_lane_where_more_are_slower(dim, shape, option, diag):
+    """Unequal masses and the diagnostic count come with four lanes or one, and four
+    are slower from 131,072 particles in 3-D and 65,536 in 2-D on; two lanes in
+    3-D are from 245,760 on, with options from 184,320 on.  There the default
+    launch has the bits of one lane."""
     c = _case(dim, shape, option)
     n, P = c.n, S.make_params(c.params)
     assert (131072 if dim == 3 else 65536) < n <= 327680
