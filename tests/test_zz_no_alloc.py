@@ -85,3 +85,13 @@ def test_noalloc_rejects_sizes_beyond_its_array():
     k = torch.zeros(1, dtype=torch.int32, device=DEV)
     with pytest.raises(S.SphError, match="invalid argument"):
         S.sph_interact_noalloc(P, n, st, k, k, x, x)
+
+
+@pytest.mark.parametrize("diag", [False, True])
+def test_noalloc_matches_interact_with_one_lane_by_size(diag):
+    """A case above the 245,760 particles up to which 3-D cases get several lanes
+    per target: the one-lane kernels, without a flag that asks for them."""
+    big = cases.dam_break_3d(dp=0.6 / 70, cell_div=2, x_sub=4)
+    assert 245_760 < big.n <= S.SPH_NOALLOC_MAX_N
+    _say(f"noalloc: diag={diag} n={big.n}")
+    _compare(big, 3, S.SPH_DIAG_COUNT_F64 if diag else 0)
