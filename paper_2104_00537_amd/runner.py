@@ -70,7 +70,9 @@ class Simulation:
         self.interactions = torch.zeros(2, dtype=torch.int64, device=dev)
         self.steps_done = 0
         self.graph = None
-        # with `timing`, record events around these calls only (None: all)
+        # with `timing`, record events around these calls only (None: all).  The
+        # parts of the one-call update ("reduce_dt", "symplectic", "refresh_view")
+        # run apart when one of them is recorded; it is "update" itself
         self.timed_calls = None
         # sph_interact flags: 0 for the production pass, or a precision-study
         # arm (S.SPH_INTERACT_F64 / S.SPH_INTERACT_ABS_F32)
@@ -240,12 +242,15 @@ class Simulation:
         else:
             call("interact", S.sph_interact, P, n, b, self.key, self.cell_start, self.ace,
                  self.arho, self.ws, flags=self.flags, stream=stream)
-        # dt, update and refresh in one call, unless each is timed by itself or
-        # the floating bodies' step comes between them
-        fused = timing is None and self.bodies is None and not self.params.floating
+        # dt, update and refresh in one call, unless one of them is timed by
+        # itself or the floating bodies' step comes between them
+        apart = timing is not None and (not self.timed_calls or any(
+            k in self.timed_calls for k in ("reduce_dt", "symplectic", "refresh_view")))
+        fused = not apart and self.bodies is None and not self.params.floating
         if fused:
-            S.sph_symplectic_update(P, n, 0, self.dt, self.dt_half, self.interactions, self.t, s0,
-                                    b, self.ace, self.arho, self.key, self.ws, stream=stream)
+            call("update", S.sph_symplectic_update, P, n, 0, self.dt, self.dt_half,
+                 self.interactions, self.t, s0, b, self.ace, self.arho, self.key, self.ws,
+                 stream=stream)
         else:
             call("reduce_dt", S.sph_reduce_dt, P, n, self.dt, self.ws,
                  interactions=self.interactions, stream=stream)
@@ -259,16 +264,14 @@ class Simulation:
             call("interact", S.sph_interact_list, P, n, b, self.key, self.cell_start, self.list,
                  self.ace, self.arho, self.ws, flags=self.flags | S.SPH_INTERACT_REUSE_CELLS,
                  stream=stream)
-        elif fused and self.fused_conc:
-            S.sph_interact_conc(P, n, b, self.key, self.cell_start, self.ace, self.arho, self.ws,
-                                flags=self.flags | S.SPH_INTERACT_REUSE_CELLS, stream=stream)
         else:
-            call("interact", S.sph_interact, P, n, b, self.key, self.cell_start, self.ace,
-                 self.arho, self.ws, flags=self.flags | S.SPH_INTERACT_REUSE_CELLS,
-                 stream=stream)
+            call("interact", S.sph_interact_conc if self.fused_conc else S.sph_interact, P, n, b,
+                 self.key, self.cell_start, self.ace, self.arho, self.ws,
+                 flags=self.flags | S.SPH_INTERACT_REUSE_CELLS, stream=stream)
         if fused:
-            S.sph_symplectic_update(P, n, 1, self.dt, self.dt_half, self.interactions, self.t, s0,
-                                    b, self.ace, self.arho, self.key, self.ws, stream=stream)
+            call("update", S.sph_symplectic_update, P, n, 1, self.dt, self.dt_half,
+                 self.interactions, self.t, s0, b, self.ace, self.arho, self.key, self.ws,
+                 stream=stream)
         else:
             call("reduce_dt", S.sph_reduce_dt, P, n, self.dt_half, self.ws,
                  interactions=self.interactions, stream=stream)
@@ -277,12 +280,10 @@ class Simulation:
             if self.bodies is not None:
                 call("floating", S.sph_floating_step, P, n, 1, self.dt, self.bodies, s0, b, self.ace,
                      self.ws, stream=stream)
-        if fused and self.fused_conc:
-            S.sph_shifting_conc(P, n, b, self.key, self.cell_start, self.dt, self.ws,
-                                stream=stream)
-        elif self.shifting:
-            call("shifting", S.sph_shifting, P, n, b, self.key, self.cell_start, self.dt, self.ws,
-                 flags=S.SPH_INTERACT_REUSE_CELLS, stream=stream)
+        if self.shifting:
+            call("shifting", S.sph_shifting_conc if self.fused_conc else S.sph_shifting, P, n, b,
+                 self.key, self.cell_start, self.dt, self.ws, flags=S.SPH_INTERACT_REUSE_CELLS,
+                 stream=stream)
         self.states = [b, a]
         self.steps_done += 1
 

@@ -111,6 +111,35 @@ def test_one_call_matches_the_separate_calls(kind, n):
             assert err <= tol * scale, (kind, tol, err, scale)
 
 
+def test_timing_other_calls_leaves_the_step_as_it_is():
+    """Events around the interactions alone, as the benchmark records them: the
+    step takes the one-call update and the fused concentration as without, bit for
+    bit (a size at which shifting by itself would sum C over another number of
+    lanes).  Timed call by call, the update's parts run apart: one rounding of
+    FP32 in the velocities, of which positions take a time step's share."""
+    out = []
+    for timed in ("none", "interact", "all"):
+        c = cases.block_case(3, (34, 32, 26), walls=True, cell_div=2, x_sub=4, seed=5)
+        c.params = dataclasses.replace(c.params, shift_coef=2.0, shift_fs=0.9)
+        rng = np.random.default_rng(3)
+        c.vel[:] = rng.uniform(-0.3, 0.3, c.vel.shape).astype(np.float32)
+        sim = Simulation(c, DEV)
+        timing = None if timed == "none" else {}
+        sim.timed_calls = ("interact",) if timed == "interact" else None
+        for _ in range(3):
+            sim.step(timing=timing)
+        torch.cuda.synchronize()
+        assert sim.error() == 0
+        if timed == "interact":
+            assert {k: len(v) for k, v in timing.items()} == {"interact": 6}
+        if timed == "all":
+            assert "update" not in timing and len(timing["shifting"]) == 3
+        out.append((sim.state.pos, sim.state.vel, sim.state.rho))
+    assert all(torch.equal(x, y) for x, y in zip(out[0], out[1]))
+    for x, y, tol in zip(out[0], out[2], (1e-9, 1e-5, 1e-5)):
+        assert (x - y).abs().max().item() <= tol * y.abs().max().item()
+
+
 def test_one_buffer_for_both_time_steps():
     """dt_half = dt: the second pass's time step is written before the corrector
     reads it, as in the separate calls; every result equals theirs."""
