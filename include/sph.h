@@ -262,7 +262,11 @@ size_t sph_workspace_bytes(const sph_params* p, int64_t n);
  *   carry_in/out      nullable pair: a second state (pos, vel, rho only)
  *                     gathered by the same perm -- the saved state n during
  *                     the corrector's NL.
- * `in` and `out` must not alias. */
+ * `in` and `out` must not alias.
+ * The sort costs each cell the square of its population, unless the grid is
+ * coarse (a cell filled at density rho0, or the mean cell, holds more than 160
+ * particles), where it does not depend on it; only particles crowded into a
+ * cell far beyond rho0 pay that square. */
 sph_status sph_bin_cells(const sph_params* p, int64_t n, const sph_state* in,
                          sph_state* out, const sph_state* carry_in,
                          sph_state* carry_out, uint32_t* key, uint32_t* perm,
@@ -626,7 +630,11 @@ enum {
   /* some slot has periodic components (Section 2.7): the interaction and
    * shifting then take the nearest image along each slot's own periodic
    * components; slots without any see no difference. */
-  SPH_BATCH_PERIODIC = 8u
+  SPH_BATCH_PERIODIC = 8u,
+  /* some slot's cells are coarse: the binning then takes the sort whose cost does
+   * not depend on the cells' population (see sph_bin_cells), with the same
+   * results. */
+  SPH_BATCH_COARSE = 16u
 };
 
 typedef struct sph_batch {
@@ -657,8 +665,9 @@ size_t sph_batch_table_bytes(int32_t n_slots);
  * options: 0 or SPH_BATCH_FOUR_LANES (else SPH_E_ARG); batch->flags gets
  * SPH_BATCH_WAVE_ALIGNED when every range is whole wavefronts,
  * SPH_BATCH_FOUR_LANES when it was asked for and the batch is wave-aligned,
- * SPH_BATCH_GENERAL when some slot takes a formulation option and
- * SPH_BATCH_PERIODIC when some slot has periodic components. */
+ * SPH_BATCH_GENERAL when some slot takes a formulation option,
+ * SPH_BATCH_PERIODIC when some slot has periodic components and
+ * SPH_BATCH_COARSE when some slot's cells are coarse. */
 sph_status sph_batch_describe(const sph_params* params, const int64_t* offsets, int32_t n_slots,
                               uint32_t options, void* table_host, size_t table_bytes,
                               sph_batch* batch);

@@ -229,8 +229,9 @@ sph_status sph_bin_cells(const sph_params* p, int64_t n, const sph_state* in, sp
   if (ws_bytes < ws_layout(n).total) return SPH_E_WORKSPACE;
   const KParams kp = make_kparams(*p);
   sph_state i0 = n > 0 ? *in : sph_state{}, o0 = n > 0 ? *out : sph_state{};
-  return hip_status(launch_bin_cells(kp, n, i0, o0, carry_in, carry_out, key, perm, cell_start,
-                                     ws, (hipStream_t)stream));
+  const auto launch = coarse_cells(*p, n) ? launch_bin_cells_radix : launch_bin_cells;
+  return hip_status(launch(kp, n, i0, o0, carry_in, carry_out, key, perm, cell_start, ws,
+                           (hipStream_t)stream));
 }
 
 // The interaction walk addresses the views and the cell ranges with 32-bit
@@ -519,7 +520,7 @@ sph_status sph_batch_describe(const sph_params* params, const int64_t* offsets, 
   if (offsets[0] != 0) return SPH_E_ARG;
   SlotEntry* tab = (SlotEntry*)table_host;
   uint64_t cbase = 0;
-  bool general = false, periodic = false;
+  bool general = false, periodic = false, coarse = false;
   for (int s = 0; s < n_slots; ++s) {
     const sph_params* p = &params[s];
     if (!params_ok(p) || p->cell_div != params[0].cell_div) return SPH_E_ARG;
@@ -531,6 +532,7 @@ sph_status sph_batch_describe(const sph_params* params, const int64_t* offsets, 
     if (per && !periodic_reach_ok(p, p->cell_div + 1)) return SPH_E_ARG;
     general = general || p->kernel != 0 || p->viscosity != 0 || p->ddt == 2;
     periodic = periodic || per;
+    coarse = coarse || coarse_cells(*p, offsets[s + 1] - offsets[s]);
     if (offsets[s + 1] < offsets[s]) return SPH_E_ARG;
     SlotEntry e{};
     e.kp = make_slot_kparams(*p);
@@ -556,7 +558,8 @@ sph_status sph_batch_describe(const sph_params* params, const int64_t* offsets, 
   }
   batch->n_slots = n_slots;
   batch->flags = (aligned ? SPH_BATCH_WAVE_ALIGNED : 0u) | (four ? SPH_BATCH_FOUR_LANES : 0u) |
-                 (general ? SPH_BATCH_GENERAL : 0u) | (periodic ? SPH_BATCH_PERIODIC : 0u);
+                 (general ? SPH_BATCH_GENERAL : 0u) | (periodic ? SPH_BATCH_PERIODIC : 0u) |
+                 (coarse ? SPH_BATCH_COARSE : 0u);
   batch->lanes = (uint32_t)lanes;
   batch->cell_div = params[0].cell_div;
   batch->n_total = offsets[n_slots];
@@ -585,8 +588,10 @@ sph_status sph_batch_bin_cells(const sph_batch* b, const sph_state* in, sph_stat
     return SPH_E_ARG;
   if (ws_bytes < batch_ws_layout(b->n_slots, n).total) return SPH_E_WORKSPACE;
   sph_state i0 = n > 0 ? *in : sph_state{}, o0 = n > 0 ? *out : sph_state{};
-  return hip_status(launch_batch_bin_cells(batch_desc(b), i0, o0, carry_in, carry_out, key, perm,
-                                           cell_start, ws, (hipStream_t)stream));
+  const bool coarse = (b->flags & SPH_BATCH_COARSE) != 0 && n >= kCoarseMinN;
+  const auto launch = coarse ? launch_batch_bin_cells_radix : launch_batch_bin_cells;
+  return hip_status(launch(batch_desc(b), i0, o0, carry_in, carry_out, key, perm, cell_start, ws,
+                           (hipStream_t)stream));
 }
 
 sph_status sph_batch_interact(const sph_batch* b, const sph_state* s, const uint32_t* key,

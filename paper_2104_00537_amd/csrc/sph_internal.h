@@ -171,6 +171,27 @@ inline bool walk_fits_32(int64_t n, uint64_t cells) {
   return n < ((int64_t)1 << 28) - 4 && cells < ((uint64_t)1 << 30);
 }
 
+// Whether n particles on the case's grid are binned by the radix sort
+// (sph_bin_radix.hip) and not by the counting sort: whether a cell that fluid
+// fills, or the mean one, holds more than kCoarseMembers of them.  Measured (us,
+// counting / radix sort; input as a step leaves it, and in random order):
+//   3-D, 33 a cell   1.35M  66 / 120, 322 / 313   (a filled cell: 42)
+//        245         1.35M  131 / 123, 350 / 305  (333)
+//        1854        1.35M  545 / 99, 969 / 274
+//        21840       175k   6004 / 29, 6662 / 31
+//   2-D, 126         1.09M  69 / 109, 245 / 212   (128)
+//        492         1.09M  139 / 113, 323 / 212  (512)
+constexpr double kCoarseMembers = 160.0;
+constexpr int64_t kCoarseMinN = 64;
+inline bool coarse_cells(const sph_params& p, int64_t n) {
+  if (n < kCoarseMinN) return false;
+  double volume = p.cell_size * p.cell_size / p.x_sub;
+  if (p.dim == 3) volume *= p.cell_size;
+  const double mass = p.mass_fluid < p.mass_bound ? p.mass_fluid : p.mass_bound;
+  const double cells = (double)p.ncell[0] * p.ncell[1] * p.ncell[2];
+  return volume * p.rho0 > kCoarseMembers * mass || (double)n > kCoarseMembers * cells;
+}
+
 // Workspace layout (offsets in bytes, each region 256-aligned).
 struct WsLayout {
   size_t err;        // the WsHeader (offset 0)

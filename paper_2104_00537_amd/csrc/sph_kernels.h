@@ -28,6 +28,10 @@ void launch_scan_cells(uint32_t* cell_start, int64_t cells, uint32_t* xcount, in
 hipError_t launch_bin_cells(const KParams& kp, int64_t n, const sph_state& in, sph_state& out,
                             const sph_state* cin, sph_state* cout, uint32_t* key,
                             uint32_t* perm, uint32_t* cell_start, void* ws, hipStream_t st);
+hipError_t launch_bin_cells_radix(const KParams& kp, int64_t n, const sph_state& in,
+                                  sph_state& out, const sph_state* cin, sph_state* cout,
+                                  uint32_t* key, uint32_t* perm, uint32_t* cell_start, void* ws,
+                                  hipStream_t st);
 hipError_t launch_refresh_view(const KParams& kp, int64_t n, const sph_state& s,
                                const uint32_t* key, void* ws, hipStream_t st);
 hipError_t launch_interact(const KParams& kp, int64_t n, const sph_state& s, const uint32_t* key,
@@ -85,6 +89,10 @@ hipError_t launch_clear_error(void* ws, hipStream_t st);
 hipError_t launch_batch_bin_cells(const BatchDesc& B, const sph_state& in, sph_state& out,
                                   const sph_state* cin, sph_state* cout, uint32_t* key,
                                   uint32_t* perm, uint32_t* cell_start, void* ws, hipStream_t st);
+hipError_t launch_batch_bin_cells_radix(const BatchDesc& B, const sph_state& in, sph_state& out,
+                                        const sph_state* cin, sph_state* cout, uint32_t* key,
+                                        uint32_t* perm, uint32_t* cell_start, void* ws,
+                                        hipStream_t st);
 hipError_t launch_batch_interact(const BatchDesc& B, const uint32_t* key,
                                  const uint32_t* cell_start, float* ace, float* arho, float* visc,
                                  uint32_t* nbr, bool reuse, void* ws, hipStream_t st);
