@@ -52,9 +52,12 @@ struct ShiftAcc {
 
 // One group of 4 consecutive candidates from byte offset o of the view (see
 // gather_group): positions loaded together and tested, then for the gradient
-// the concentrations of the hits, then their terms.  LAST: only the candidates
-// before byte offset o1 count (the view is padded by kViewPad entries).
-template <int DIM, bool GRAD, bool LAST, typename O>
+// the concentrations of the hits, then their terms.  Only the candidates before
+// byte offset o1 count (the view is padded by kViewPad entries): whole groups in a
+// loop of their own and a masked one behind it made a wavefront take a round more
+// per row than its longest lane needs (1.37M particles of a batch, both kernels:
+// 803 us, masked throughout 741).
+template <int DIM, bool GRAD, typename O>
 __device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, float ys, float zs,
                                             O o, O o1, const float4* __restrict__ pr,
                                             const float* __restrict__ conc, float ca,
@@ -67,7 +70,7 @@ __device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, floa
 #pragma unroll
   for (int u = 0; u < NU; ++u) {
     r2s[u] = pair_geom<DIM>(kp, xa, ys, zs, pb[u], dxs[u], dys[u], dzs[u]);
-    hit[u] = r2s[u] < kp.support2_f && (!LAST || o + 16u * u < o1);
+    hit[u] = r2s[u] < kp.support2_f && o + 16u * u < o1;
     // (the density is loaded with the position: left alone, the compiler loads
     // it by itself once the test has passed)
     asm volatile("" ::"v"(pb[u].w));
@@ -97,8 +100,8 @@ __device__ __forceinline__ void shift_group(const KParams& kp, uint32_t xa, floa
 }
 
 // The sums of one target (view position pa, key cell (cx, cy, cz), cell keys
-// offset by cbase) over the rows of lane `sub` of its LPT (walk_rows): each
-// range as whole groups of 4 and a masked one.
+// offset by cbase) over the rows of lane `sub` of its LPT (walk_rows), in masked
+// groups of 4.
 template <int DIM, int R, bool PER, bool GRAD, int LPT, bool WIDE>
 __device__ __forceinline__ ShiftAcc<DIM, GRAD> shift_walk(const KParams& kp, uint32_t cbase,
                                                const float4& pa, int cx, int cy, int cz,
@@ -108,9 +111,8 @@ __device__ __forceinline__ ShiftAcc<DIM, GRAD> shift_walk(const KParams& kp, uin
                                                int sub, int stride) {
   ShiftAcc<DIM, GRAD> acc{};
   auto walk = [&](auto o, auto o1, uint32_t xv, float ys, float zs) {
-    for (; o + 64u <= o1; o += 64u)
-      shift_group<DIM, GRAD, false>(kp, xv, ys, zs, o, o1, pr, conc, ca, acc);
-    if (o < o1) shift_group<DIM, GRAD, true>(kp, xv, ys, zs, o, o1, pr, conc, ca, acc);
+    for (; o < o1; o += 64u)
+      shift_group<DIM, GRAD>(kp, xv, ys, zs, o, o1, pr, conc, ca, acc);
   };
   walk_rows<DIM, R, PER, LPT, WIDE>(kp, cbase, pa, cx, cy, cz, cstart, cull2, sub, stride, walk);
   return acc;
@@ -140,7 +142,6 @@ __device__ inline void target_cell(const KParams& kp, uint32_t k, int& cx, int& 
   cz = (int)(rest / (uint32_t)kp.ncy);
 }
 
-// C_a = sum_b V_b W_ab (Eq. 53), every non-excluded particle, a included.
 // The culling radius squared of a walk: the support (with a margin above the
 // FP32 error of the offsets) when the cells are those of the view's own
 // binning; widened by the largest recorded displacement when they are reused
@@ -163,7 +164,8 @@ __device__ inline float shift_cull2(const KParams& kp, const uint32_t* __restric
   return rc * rc;
 }
 
-// C_a of one target (local key lk, cell keys offset by cbase) in every lane of
+// C_a = sum_b V_b W_ab (Eq. 53), every non-excluded particle, a included, of one
+// target (cell keys offset by cbase) in every lane of
 // its LPT; lanes without a target (`live` false) take part in the sums over lanes.
 template <int DIM, int R, bool PER, int LPT, bool WIDE>
 __device__ inline float conc_one(const KParams& kp, bool live, uint32_t cbase, int64_t i,
@@ -314,7 +316,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_shift(
     const int rs = __builtin_amdgcn_readlane(sa, leader);
     const bool mine = todo && sa == rs;
     todo = todo && !mine;
-    const KParams& kp = tab[rs].kp;
+    // (a copy: the walk's asm statement would have the table read again after it,
+    // which cost a batch of 68k particles 186 us in place of 160)
+    const KParams kp = tab[rs].kp;
     if (!(kp.shift_k_f > 0.f)) {  // no shifting in this slot
       if (mine && !APPLY) conc[i] = 0.f;
       if (mine && APPLY && shift)
@@ -343,12 +347,13 @@ __global__ __launch_bounds__(kBlock) void k_batch_shift(
 // Lanes per target for a case of n particles, as for the interaction
 // (lanes_per_target), of fewer kinds.  Measured, both kernels together, us with
 // 1 / 4 / 16 lanes (dam breaks on reused cells):
-//   3-D    6k: 168 / 70 / 34    25k: 174 / 71 / 48    38k: 173 / 74 / 65
-//         66k: 180 / 87 / 97   127k: 188 / 144 / 173  168k: 192 / 189 / 234
-//   2-D    4k: 27 / 16          54k: 29 / 23           84k: 30 / 31
+//   3-D    7k: 166 / 69 / 32    21k: 167 / 67 / 41    33k: 163 / 69 / 54
+//         58k: 169 / 79 / 88   127k: 175 / 136 / 166  168k: 182 / 179 / 225
+//         filled box          140k: 186 / 183 / 236  175k: 210 / 230 / 289
+//   2-D    4k: 26 / 16          54k: 27 / 22           84k: 29 / 29
 static int shift_lanes(int dim, int64_t n) {
   if (dim == 2) return n <= 65536 ? 4 : 1;
-  return n <= 49152 ? 16 : n <= 163840 ? 4 : 1;
+  return n <= 49152 ? 16 : n <= 147456 ? 4 : 1;
 }
 
 hipError_t launch_shifting(const KParams& kp, int64_t n, const sph_state& s, const uint32_t* key,
