@@ -28,15 +28,6 @@ __device__ __forceinline__ void target_data(const KParams& kp, int64_t i,
   T.flt = GEN && kp.floating && is_floating(type[i]);
 }
 
-// Cell coordinates (in key cells) of key k.
-__device__ __forceinline__ void key_cell(const KParams& kp, uint32_t k, int& cx, int& cy,
-                                         int& cz) {
-  cx = (int)(k % (uint32_t)kp.ncx);
-  const uint32_t rest = k / (uint32_t)kp.ncx;
-  cy = (int)(rest % (uint32_t)kp.ncy);
-  cz = (int)(rest / (uint32_t)kp.ncy);
-}
-
 // Wavefronts per SIMD that the registers are held to (1: not held).  The walk
 // fills its waits with other wavefronts, and a case of few rounds of wavefronts
 // ends on a partly filled one, so that one more or less per SIMD shows (us per
@@ -101,21 +92,10 @@ k_interact_gather(
       // with modified DBC the wall densities come from Eq. 38 (sph_mdbc): wall
       // targets take no sums
       if (!is_excluded(type[i]) && (kp.boundary == 0 || is_fluid(type[i]))) {
-        const float4 pa = pr[i], va = vp[i];
-        T.fluid = pa.w > 0.f;
-        T.rho = fabsf(pa.w);
-        T.irho = __builtin_amdgcn_rcpf(T.rho);
-        T.ik = kp.kvc_f * T.irho;
-        T.p = va.w;
-        T.vx = va.x;
-        T.vy = va.y;
-        T.vz = va.z;
-        T.flt = GEN && kp.floating && is_floating(type[i]);
-        const uint32_t k = key[i];
-        const int cx = (int)(k % (uint32_t)kp.ncx);
-        const uint32_t rest = k / (uint32_t)kp.ncx;
-        const int cy = (int)(rest % (uint32_t)kp.ncy);
-        const int cz = (int)(rest / (uint32_t)kp.ncy);
+        target_data<GEN>(kp, i, pr, vp, type, T);
+        const float4 pa = pr[i];
+        int cx, cy, cz;
+        key_cell(kp, key[i], cx, cy, cz);
         gather_walk<DIM, R, DIAG, EQM, GEN, PER, 1, CONC>(kp, 0u, n, i, pa, T, cx, cy, cz, pr, vp,
                                                           cstart, pos64, acc, c64, cull2);
         if (T.fluid) acc.cnt -= 1u;  // the self pair: counted, added nothing

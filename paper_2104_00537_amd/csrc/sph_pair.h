@@ -325,6 +325,15 @@ __device__ __forceinline__ void gather_group(const KParams& kp, int64_t n, int64
       pair_terms<DIM, EQM, GEN, CONC>(kp, T, dxs[u], dys[u], dzs[u], r2s[u], pb[u].w, vb[u], acc);
 }
 
+// Cell coordinates (in key cells) of key k.
+__device__ __forceinline__ void key_cell(const KParams& kp, uint32_t k, int& cx, int& cy,
+                                         int& cz) {
+  cx = (int)(k % (uint32_t)kp.ncx);
+  const uint32_t rest = k / (uint32_t)kp.ncx;
+  cy = (int)(rest % (uint32_t)kp.ncy);
+  cz = (int)(rest / (uint32_t)kp.ncy);
+}
+
 // The candidate walk of one target lane over the rows of its neighbour cells
 // (cell indices offset by cbase).  The key cells of a row along x (2R+1
 // cells of cs, each split into x_sub key cells) are consecutive in the sorted

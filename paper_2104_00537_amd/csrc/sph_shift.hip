@@ -135,13 +135,6 @@ __device__ inline int64_t shift_lane(const WsHeader* __restrict__ hdr, int& sub,
   return lanes == 1 ? t : t / LPT;
 }
 
-__device__ inline void target_cell(const KParams& kp, uint32_t k, int& cx, int& cy, int& cz) {
-  cx = (int)(k % (uint32_t)kp.ncx);
-  const uint32_t rest = k / (uint32_t)kp.ncx;
-  cy = (int)(rest % (uint32_t)kp.ncy);
-  cz = (int)(rest / (uint32_t)kp.ncy);
-}
-
 // The culling radius squared of a walk: the support (with a margin above the
 // FP32 error of the offsets) when the cells are those of the view's own
 // binning; widened by the largest recorded displacement when they are reused
@@ -177,7 +170,7 @@ __device__ inline float conc_one(const KParams& kp, bool live, uint32_t cbase, i
   if (live) {
     const float4 pa = pr[i];
     int cx, cy, cz;
-    target_cell(kp, key[i] - cbase, cx, cy, cz);
+    key_cell(kp, key[i] - cbase, cx, cy, cz);
     acc = shift_walk<DIM, R, PER, false, LPT, WIDE>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
                                                     nullptr, 0.f, sub, lanes);
   }
@@ -203,7 +196,7 @@ __device__ inline void shift_one(const KParams& kp, bool live, uint32_t cbase, i
     ca = conc[i];
     const float4 pa = pr[i];
     int cx, cy, cz;
-    target_cell(kp, key[i] - cbase, cx, cy, cz);
+    key_cell(kp, key[i] - cbase, cx, cy, cz);
     acc = shift_walk<DIM, R, PER, true, LPT, WIDE>(kp, cbase, pa, cx, cy, cz, pr, cstart, cull2,
                                                    conc, ca, sub, lanes);
   }
