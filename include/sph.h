@@ -132,7 +132,7 @@ enum {
    * (else SPH_E_ARG), so that the longer walk meets no cell twice. */
   SPH_INTERACT_REUSE_CELLS = 8u,
   /* One lane per target particle.  By default a case too small to fill the
-   * GPU (at most 245,760 particles in 3-D, 122,880 in 2-D) deals each
+   * GPU (at most 266,240 particles in 3-D, 122,880 in 2-D) deals each
    * target's neighbour rows to 2, 4, 8 or 16 lanes, the more the smaller it
    * is, and sums their results, which shortens each lane's chain of dependent
    * loads; results agree up to the order of the FP32 sums (FP64 counts are

@@ -37,13 +37,15 @@ __device__ __forceinline__ void target_data(const KParams& kp, int64_t i,
 //   3-D, 1.32M: 7 573 / 576, 8 (it spills) 591 / 593; 1.58M: 699 / 703, 723 / 723
 //   3-D periodic, 958k: 6 604 / 610, 7 574 / 579, 8 621 / 630
 //   3-D with options, 441k: 5 304 / 307, 6 266 / 268, 7 271 / 272
+// At other sizes from 230k to 2M particles these numbers are within 2 % of the
+// compiler's own or faster.
 // With several lanes per target the registers are left to the compiler, which
 // gives the 2 lanes of the default formulation in 3-D 6 wavefronts.  A case of more
-// wavefronts than that (HOLD, from kHoldMinN particles on) ends on a second round
-// of few of them and is faster held to 7, a smaller one slower (us per pass, 6 / 7:
-// filled box 192k 131 / 131, 221k 165 / 142; dam break 153k 96 / 97, on reused cells
-// 102 / 105).
-constexpr int64_t kHoldMinN = 6 * kSimds * 64 / 2;
+// wavefronts than that ends on a second round of few of them and, from kHoldMinN
+// particles on (HOLD), is faster held to 7 (us per pass, 6 / 7: open block 207k
+// 167 / 143, 229k 178 / 153; filled box 221k 165 / 142; dam break, half of it walls
+// whose targets end early, 216k 120 / 123, 234k 129 / 135, 253k 144 / 139).
+constexpr int64_t kHoldMinN = 221184;
 constexpr int gather_waves(int dim, bool plain, bool gen, int lpt, bool hold) {
   if (hold) return 7;
   if (!plain || (dim == 2 && gen) || (dim == 3 && lpt > 1)) return 1;
@@ -155,17 +157,24 @@ k_interact_gather(
 //        223k: 164 / 124 / 144 / 158 / 189  441k: 220 / 234 / 292 / 321 / 387
 //   2-D   14k: 17 / 12 / 9.7 / 9.6 / 10     54k: 18 / 14 / 15 / 16 / 24
 //        185k: 25 / 27 / 33 / 41 / 69
-// The last line of 3-D is that of a filled box, whose targets are nearly all fluid,
-// and of the pass on reused cells (1 / 2 lanes, held as above from 197k on; the dam
-// break, half of it walls, crosses at about 300k):
-//   filled box, reused cells   221k: 179 / 155   244k: 185 / 186   260k: 190 / 200
-//   open block, reused cells   229k: 175 / 164   252k: 189 / 201
-//   dam break, reused cells    216k: 165 / 135   273k: 162 / 157   315k: 183 / 195
-// With options (gen) two lanes have 5 wavefronts per SIMD and lose sooner: reused
-// cells, cubic spline 173k: 206 / 179   184k: 198 / 193   192k: 203 / 208.
-inline int lanes_per_target(int dim, int64_t n, bool gen) {
+// The last lines of 3-D differ with the kind of case, the more so as a step's second
+// pass, on reused cells, is slower with two lanes (us, both passes, 1 / 2 lanes, held
+// as above):
+//   sloshing tank   242k: 328 / 280   266k: 350 / 306
+//   dam break       253k: 314 / 286   273k: 321 / 300   315k: 363 / 377
+//   filled box      221k: 356 / 296   244k: 366 / 359   260k: 374 / 387
+//   open block      229k: 344 / 317   252k: 375 / 385   286k: 407 / 440
+// With options (gen) two lanes have 5 wavefronts per SIMD and lose sooner (cubic
+// spline, periodic with all options):
+//   dam break       234k: 397 / 347   253k: 393 / 390
+//   sloshing tank   219k: 382 / 364   242k: 391 / 403
+//   filled box      184k: 394 / 373   192k: 402 / 399   229k: 427 / 441
+//   channel         202k: 548 / 533   209k: 548 / 546   223k: 490 / 532
+// The lines lie where no kind loses more than about 5 %.
+inline int lanes_per_target(int dim, int64_t n, bool gen, bool per) {
   if (dim == 2) return n <= 32768 ? 4 : n <= 122880 ? 2 : 1;
-  return n <= 24576 ? 16 : n <= 65536 ? 8 : n <= 98304 ? 4 : n <= (gen ? 184320 : kLanesMaxN) ? 2 : 1;
+  if (n <= 98304) return n <= 24576 ? 16 : n <= 65536 ? 8 : 4;
+  return n <= (!gen ? kLanesMaxN : per ? 212992 : 235520) ? 2 : 1;
 }
 
 template <int DIM>
@@ -179,7 +188,7 @@ hipError_t launch_gather(const KParams& kp, int64_t n, const sph_state& s, const
   const bool eqm = kp.mass_f == kp.mass_b;
   const bool gen = kp.kernel != 0 || kp.viscosity != 0 || kp.ddt == 2 || kp.floating != 0;
   const bool per = kp.periodic != 0;
-  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n, gen);
+  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n, gen, per);
   const bool hold = n > kHoldMinN;
   // the diagnostic count and unequal masses come with one lane or four, and lose
   // with four sooner (us per pass, 1 / 4 lanes):

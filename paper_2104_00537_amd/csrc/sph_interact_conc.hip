@@ -14,15 +14,15 @@ hipError_t launch_interact_conc(const KParams& kp, int64_t n, const sph_state& s
                                 hipStream_t st) {
   const WsLayout L = ws_layout(n);
   float* c = conc ? conc : ws_ptr<float>(ws, L.keyA);
-  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n, false);
-  // C takes registers: 5 wavefronts of two lanes per target in a periodic channel,
-  // so that they are held to 7 sooner than without it, and one lane is faster as
-  // soon as 7 do not hold the case (us per pass, two lanes 5 / 7 wavefronts, one:
-  // channel 168k 179 / 195, 228; 194k 252 / 223, 243; filled box 173k 141 / 145, 175;
-  // 192k 149 / 151, 170; 238k - / 195, 182)
-  const bool hold = n > 184320;
-  if (lanes == 2 && kp.dim == 3 && n > 7 * kSimds * 64 / 2) lanes = 1;
   const bool per = kp.periodic != 0;
+  int lanes = (flags & SPH_INTERACT_ONE_LANE) ? 1 : lanes_per_target(kp.dim, n, false, per);
+  // C takes registers: in a periodic channel two lanes per target have 5 wavefronts
+  // per SIMD and are held to 7 sooner than without it, and one lane is faster sooner
+  // (us per pass, two lanes / held / one: channel 168k 179 / 195 / 228, 194k 252 / 223
+  // / 243; filled box 192k 149 / 151 / 170, 238k 200 / 195 / 182; dam break 234k 149
+  // / - / 171, 253k 164 / - / 169)
+  const bool hold = n > (per ? 184320 : kHoldMinN);
+  if (lanes == 2 && kp.dim == 3 && n > (per ? 229376 : 235520)) lanes = 1;
 #define SPH_CONC(D, RR, PE, LP, HO)                                                            \
   hipLaunchKernelGGL((k_interact_gather<D, RR, false, true, false, PE, LP, true, HO>),         \
                      dim3((unsigned)((n * LP + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,    \

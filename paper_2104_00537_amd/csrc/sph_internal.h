@@ -15,7 +15,6 @@ constexpr int kScanTile = kBlock * kScanItems;
 constexpr int kScanBlocks = 2048;  // most blocks (chunks) of the scan of the cells
 constexpr int kViewPad = 8;        // spare float4 entries after each interaction view
 constexpr int kFrameCells = 8;     // x offsets in the views are taken per block of 8 cells
-constexpr int kSimds = 1024;       // SIMDs of the MI355X (256 CUs of 4)
 constexpr uint32_t kXcds = 8;      // accelerator complex dies of the MI355X
 constexpr int kFloatParts = 32;    // blocks per floating body in its reductions
 constexpr int kFloatSums = 16;     // FP64 partial sums per block (force, torque, inertia, count)
@@ -158,7 +157,7 @@ struct SlotMotion {
 // that gets more than one (see lanes_per_target), and for a slot of a batch
 // (SPH_BATCH_FOUR_LANES) with the largest slot that gets them.
 constexpr int kMaxLanes = 16;
-constexpr int64_t kLanesMaxN = 245760;
+constexpr int64_t kLanesMaxN = 266240;
 constexpr int kBatchLanes = 4;
 constexpr int64_t kBatchLanesMaxN = 131072;
 

@@ -95,11 +95,11 @@ def _rates(P, n, dst, key, start, ws, flags):
     (3, (52, 48, 44), "unequal", False), (3, (52, 48, 44), "default", True),
     (3, (60, 60, 50), "unequal", False), (3, (60, 60, 50), "options", True),
     (2, (300, 220), "unequal", False), (2, (300, 220), "default", True),
-    (3, (64, 60, 54), "default", False), (3, (60, 56, 46), "options", False)])
+    (3, (66, 64, 58), "default", False), (3, (62, 60, 54), "options", False)])
 def test_one_lane_where_more_are_slower(dim, shape, option, diag):
     """Unequal masses and the diagnostic count come with four lanes or one, and four
     are slower from 131,072 particles in 3-D and 65,536 in 2-D on; two lanes in
-    3-D are from 245,760 on, with options from 184,320 on.  There the default
+    3-D are from 266,240 on, with options from 235,520 on.  There the default
     launch has the bits of one lane."""
     c = _case(dim, shape, option)
     n, P = c.n, S.make_params(c.params)
@@ -113,3 +113,10 @@ def test_one_lane_where_more_are_slower(dim, shape, option, diag):
     many = _rates(P, n, dst, key, start, ws, flag)
     one = _rates(P, n, dst, key, start, ws, flag | S.SPH_INTERACT_ONE_LANE)
     assert all(torch.equal(a, b) for a, b in zip(many, one))
+
+
+@pytest.mark.parametrize("option", ["default", "periodic"])
+def test_two_lanes_held_to_more_wavefronts(option):
+    """The two-lane kernels of the largest cases that take them (from 221,184
+    particles on), against one lane."""
+    test_lanes_agree_with_one(3, (66, 62, 56) if option == "periodic" else (62, 60, 54), 2, option)

@@ -148,3 +148,9 @@ def test_shifting_takes_one_lane_after_a_pass_that_did(kind):
         out.append((conc, shift))
     assert S.sph_read_error(ws) == 0
     assert all(torch.equal(x, y) for x, y in zip(*out))
+
+
+def test_concentration_with_two_lanes_held_to_more_wavefronts():
+    """As test_concentration_of_the_interaction, of the two-lane kernel from 221,184
+    to 235,520 particles."""
+    test_concentration_of_the_interaction(3, (62, 60, 50), "default")

@@ -89,9 +89,9 @@ def test_noalloc_rejects_sizes_beyond_its_array():
 
 @pytest.mark.parametrize("diag", [False, True])
 def test_noalloc_matches_interact_with_one_lane_by_size(diag):
-    """A case above the 245,760 particles up to which 3-D cases get several lanes
+    """A case above the 266,240 particles up to which 3-D cases get several lanes
     per target: the one-lane kernels, without a flag that asks for them."""
     big = cases.dam_break_3d(dp=0.6 / 70, cell_div=2, x_sub=4)
-    assert 245_760 < big.n <= S.SPH_NOALLOC_MAX_N
+    assert 266_240 < big.n <= S.SPH_NOALLOC_MAX_N
     _say(f"noalloc: diag={diag} n={big.n}")
     _compare(big, 3, S.SPH_DIAG_COUNT_F64 if diag else 0)
