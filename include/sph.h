@@ -132,7 +132,8 @@ enum {
    * (else SPH_E_ARG), so that the longer walk meets no cell twice. */
   SPH_INTERACT_REUSE_CELLS = 8u,
   /* One lane per target particle.  By default a case too small to fill the
-   * GPU (at most 266,240 particles in 3-D, 122,880 in 2-D) deals each
+   * GPU (at most 266,240 particles in 3-D, 122,880 in 2-D; fewer with
+   * formulation options, unequal masses or the diagnostic count) deals each
    * target's neighbour rows to 2, 4, 8 or 16 lanes, the more the smaller it
    * is, and sums their results, which shortens each lane's chain of dependent
    * loads; results agree up to the order of the FP32 sums (FP64 counts are
@@ -516,8 +517,9 @@ sph_status sph_shifting(const sph_params* p, int64_t n, sph_state* s, const uint
 
 /* sph_interact on reused cells (flags SPH_INTERACT_REUSE_CELLS, with or without
  * SPH_INTERACT_ONE_LANE) that sums the concentration C of sph_shifting in the
- * same pass, and the rest of sph_shifting with that C: the same results with one
- * walk over the neighbours less.
+ * same pass, and the rest of sph_shifting with that C: one walk over the neighbours
+ * less, and the same results up to the order of C's FP32 sum (the interaction's
+ * lanes per target and not shifting's; equal with SPH_INTERACT_ONE_LANE).
  *   conc[n]  the C of every particle, written by the first and read by the
  *            second call; null in both: the workspace's sort buffer, valid
  *            until the next sph_bin_cells.
